@@ -25,29 +25,6 @@
 
 namespace sw {
 
-constexpr int kA128Slots = 128;  // coefficients per packed row (8 lanes x 16)
-
-// Coefficient `slot` of packed row p (slot < 128: lane slot l'*16 + tau*8 + s;
-// 128: beta_p(0); 129: alpha_p(64)) from the FP32 spectrum spec[65][Q] of U.
-__device__ __forceinline__ float2 gamma128_coef(const float2 *__restrict__ spec, int Q, int p,
-                                                int slot) {
-    int w;
-    bool use_beta;
-    if (slot < kA128Slots) {
-        const int lp = slot >> 4, tau = (slot >> 3) & 1, s = slot & 7;
-        const int f = 2 * lp + tau + 16 * s;
-        use_beta = s >= 4;
-        w = use_beta ? 128 - f : f;
-    } else {
-        use_beta = slot == kA128Slots;
-        w = use_beta ? 0 : 64;
-    }
-    const float2 *sp = spec + (int64_t)w * Q + 2 * p;
-    const float2 ue = sp[0], uo = sp[1];
-    return use_beta ? make_float2(0.5f * (ue.x + uo.y), 0.5f * (uo.x - ue.y))
-                    : make_float2(0.5f * (ue.x - uo.y), -0.5f * (ue.y + uo.x));
-}
-
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
 // a * conj-free constant (c, s): forward twiddle values are (cos, -sin)

@@ -123,20 +123,21 @@ __device__ __forceinline__ double2 trans_moment(const double *au, const double *
     return make_double2(au[2] - (c * av[2] - s * av[3]), au[3] - (s * av[2] + c * av[3]));
 }
 
-// Angle spectra of one [Q][n] table into spec[w][j] (float2, or packed bf16
-// complex when bf16 != 0).  lds: n + 2 kFftElems float2.
-template <int NT>
-__device__ void spectrum_block(const float *__restrict__ T, int n, int Q, void *spec, int bf16,
-                               const float2 *__restrict__ tw32, float2 *lds2) {
+// Angle spectra of the packed rows [pbeg, pend) of one [Q][n] table, at most
+// CH of them at a time: emit(p, w, xe, xo) gets the spectra of table rows 2p
+// and 2p + 1 at every w in [0, n/2].  Each packed row is transformed on its
+// own, so its spectra do not depend on the split.  lds: n + 2 CH n float2.
+template <int NT, typename Emit>
+__device__ void spectrum_rows(const float *__restrict__ T, int n, int pbeg, int pend, int CH,
+                              const float2 *__restrict__ tw32, float2 *lds2, Emit emit) {
     const int Wn = n / 2 + 1;
     float2 *tw = lds2;
     float2 *Z0 = lds2 + n;
-    float2 *Z1 = Z0 + kFftElems;
+    float2 *Z1 = Z0 + CH * n;
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += NT) tw[i] = tw32[i];
-    const int CH = fft_chunk_rows(n, Q);
-    for (int p0 = 0; p0 < Q / 2; p0 += CH) {
-        const int rows = min(CH, Q / 2 - p0);
+    for (int p0 = pbeg; p0 < pend; p0 += CH) {
+        const int rows = min(CH, pend - p0);
         __syncthreads();
         load_packed<NT>(Z0, T, n, p0, rows);
         __syncthreads();
@@ -145,20 +146,34 @@ __device__ void spectrum_block(const float *__restrict__ T, int n, int Q, void *
             const int w = idx / rows, pl = idx - w * rows;
             float2 xe, xo;
             unpack(Z, pl, n, w, xe, xo);
-            const int64_t o = (int64_t)w * Q + 2 * (p0 + pl);
-            if (bf16) {
-                uint32_t *sp = (uint32_t *)spec;
-                const float2 e = bf16r2(xe), d = bf16r2(xo);
-                sp[o] = (__float_as_uint(e.x) >> 16) | (__float_as_uint(e.y) & 0xffff0000u);
-                sp[o + 1] = (__float_as_uint(d.x) >> 16) | (__float_as_uint(d.y) & 0xffff0000u);
-            } else {
-                float2 *sp = (float2 *)spec;
-                sp[o] = xe;
-                sp[o + 1] = xo;
-            }
+            emit(p0 + pl, w, xe, xo);
         }
     }
     __syncthreads();
+}
+
+// The spectra of rows 2p and 2p + 1 at w into spec[w][j] (float2).
+__device__ __forceinline__ void store_spectrum(float2 *spec, int Q, int p, int w, float2 xe,
+                                               float2 xo) {
+    *(float4 *)(spec + (int64_t)w * Q + 2 * p) = make_float4(xe.x, xe.y, xo.x, xo.y);
+}
+
+// The register-FFT alignment's coefficients (align128_dev.h) of packed row p
+// at frequency w of an n = 128 table: alpha(w) = (conj xe - i conj xo) / 2 and
+// beta(w) = (conj xe + i conj xo) / 2, laid out in that kernel's lane order.
+// Frequency f (alpha at f < 64, beta of 128 - f from 64 on) sits in slot
+// 16 lp + 8 tau + s with f = 2 lp + tau + 16 s; beta(0) and alpha(64) in gx.
+constexpr int kA128Slots = 128;  // coefficients per packed row (8 lanes x 16)
+__device__ __forceinline__ void store_gamma128(float2 *gam, float2 *gx, int p, int w, float2 xe,
+                                               float2 xo) {
+    const float2 alpha = make_float2(0.5f * (xe.x - xo.y), -0.5f * (xe.y + xo.x));
+    const float2 beta = make_float2(0.5f * (xe.x + xo.y), 0.5f * (xo.x - xe.y));
+    float2 *row = gam + p * kA128Slots;
+    auto slot = [](int f) { return ((f & 14) << 3) | ((f & 1) << 3) | (f >> 4); };
+    if (w < 64) row[slot(w)] = alpha;
+    else gx[2 * p + 1] = alpha;
+    if (w > 0) row[slot(128 - w)] = beta;
+    else gx[2 * p] = beta;
 }
 
 // Alignment of one table pair by one block: spectra of V, spectral dot with

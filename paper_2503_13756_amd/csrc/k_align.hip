@@ -4,17 +4,53 @@
 
 namespace sw {
 
-template <int NT>
+// What the spectra of a table become: FP32 or packed bf16 complex spectra
+// spec[w][j], or the coefficients of the register-FFT alignment of n = 128
+// (gam, then gamx; see store_gamma128).
+enum SpectrumOut { kSpecF32, kSpecBf16, kSpecGamma };
+
+// Block (g, y) transforms the packed rows [y rows, (y + 1) rows) of table g,
+// CH at a time.  The row split is what fills the device for few tables: one
+// reference of n = Q = 128 went through one block in 40 us (149 us at 256,
+// bound by the passes' latency, 255 compute units idle), and its coefficients
+// through a second launch of 5 us; 1 vs 1,000 at L = 128 (bf16) 359 -> 325 us,
+// 1 vs 1,500 at L = 256 3.56 -> 3.42 ms.
+template <int NT, int OUT>
 __global__ __launch_bounds__(NT) void k_spectrum(const float *__restrict__ qt, int64_t N, Geo g,
-                                                 const float2 *__restrict__ tw32, void *spec,
-                                                 int bf16) {
+                                                 const float2 *__restrict__ tw32, void *out,
+                                                 int rows, int CH) {
     extern __shared__ __align__(16) float2 lds2[];
     const int64_t gi = blockIdx.x;
     if (gi >= N) return;
-    const int Wn = g.n / 2 + 1;
-    const size_t esz = bf16 ? sizeof(uint32_t) : sizeof(float2);
-    spectrum_block<NT>(qt + gi * (int64_t)g.Q * g.n, g.n, g.Q,
-                       (char *)spec + (size_t)gi * Wn * g.Q * esz, bf16, tw32, lds2);
+    const int P2 = g.Q / 2, Wn = g.n / 2 + 1, pbeg = (int)blockIdx.y * rows;
+    const float *T = qt + gi * (int64_t)g.Q * g.n;
+    const int pend = min(pbeg + rows, P2);
+    if constexpr (OUT == kSpecGamma) {
+        float2 *gam = (float2 *)out + gi * P2 * kA128Slots;
+        float2 *gx = (float2 *)out + N * P2 * kA128Slots + gi * P2 * 2;
+        spectrum_rows<NT>(T, g.n, pbeg, pend, CH, tw32, lds2,
+                          [&](int p, int w, float2 xe, float2 xo) {
+                              store_gamma128(gam, gx, p, w, xe, xo);
+                          });
+    } else if constexpr (OUT == kSpecBf16) {
+        uint32_t *sp = (uint32_t *)out + gi * Wn * g.Q;
+        spectrum_rows<NT>(T, g.n, pbeg, pend, CH, tw32, lds2,
+                          [&](int p, int w, float2 xe, float2 xo) {
+                              const float2 e = bf16r2(xe), d = bf16r2(xo);
+                              uint2 v;
+                              v.x = (__float_as_uint(e.x) >> 16) |
+                                    (__float_as_uint(e.y) & 0xffff0000u);
+                              v.y = (__float_as_uint(d.x) >> 16) |
+                                    (__float_as_uint(d.y) & 0xffff0000u);
+                              *(uint2 *)(sp + (int64_t)w * g.Q + 2 * p) = v;
+                          });
+    } else {
+        float2 *sp = (float2 *)out + gi * Wn * g.Q;
+        spectrum_rows<NT>(T, g.n, pbeg, pend, CH, tw32, lds2,
+                          [&](int p, int w, float2 xe, float2 xo) {
+                              store_spectrum(sp, g.Q, p, w, xe, xo);
+                          });
+    }
 }
 
 template <int NT>
@@ -45,17 +81,36 @@ __global__ __launch_bounds__(NT) void k_align_pairs(PairArgs a, Geo g,
     align_pair_block<NT>(job, g, a.mode, a.bf16, a.top_k, tw32, tw64, lds2);
 }
 
-hipError_t launch_spectrum(const float *qt, int64_t N, Geo g, const AngleTable &t, void *spec,
-                           int bf16, hipStream_t s) {
+// Packed rows per block: one block per table, in chunks of kFftElems, when
+// the tables alone fill the device twice over; fewer rows per block (down to
+// one) for fewer tables, about kSpectrumBlocks blocks in all.
+constexpr int kSpectrumBlocks = 512;
+
+template <int OUT>
+static hipError_t launch_spectrum_t(const float *qt, int64_t N, Geo g, const AngleTable &t,
+                                    void *out, hipStream_t s) {
     if (N <= 0) return hipSuccess;
     constexpr int NT = 256;
-    const size_t lds = sizeof(float2) * (g.n + 2 * kFftElems);
-    static const hipError_t attr = hipFuncSetAttribute(
-        (const void *)k_spectrum<NT>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-    (void)attr;
-    hipLaunchKernelGGL((k_spectrum<NT>), dim3((unsigned)N), dim3(NT), lds, s, qt, N, g, t.d32,
-                       spec, bf16);
+    const int P2 = g.Q / 2;
+    const int64_t want = N < kSpectrumBlocks ? (kSpectrumBlocks + N - 1) / N : 1;
+    const int rows = want >= P2 ? 1 : (int)((P2 + want - 1) / want);
+    int CH = kFftElems / g.n;
+    if (CH > rows) CH = rows;
+    const size_t lds = sizeof(float2) * (size_t)(g.n + 2 * CH * g.n);
+    hipLaunchKernelGGL((k_spectrum<NT, OUT>), dim3((unsigned)N, (unsigned)((P2 + rows - 1) / rows)),
+                       dim3(NT), lds, s, qt, N, g, t.d32, out, rows, CH);
     return hipGetLastError();
+}
+
+hipError_t launch_spectrum(const float *qt, int64_t N, Geo g, const AngleTable &t, void *spec,
+                           int bf16, hipStream_t s) {
+    return bf16 ? launch_spectrum_t<kSpecBf16>(qt, N, g, t, spec, s)
+                : launch_spectrum_t<kSpecF32>(qt, N, g, t, spec, s);
+}
+
+hipError_t launch_gamma128(const float *qt, int64_t N, Geo g, const AngleTable &t, float2 *gam,
+                           hipStream_t s) {
+    return launch_spectrum_t<kSpecGamma>(qt, N, g, t, gam, s);
 }
 
 hipError_t launch_align_pairs(const PairArgs &a, Geo g, const AngleTable &t, hipStream_t s) {

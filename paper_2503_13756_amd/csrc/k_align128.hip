@@ -4,23 +4,6 @@
 
 namespace sw {
 
-// Coefficients of every reference: gam[r][p][slot] and gamx[r][p][0..1]
-// (see gamma128_coef).  spec: FP32 spectra [n_ref][65][Q].
-__global__ __launch_bounds__(256) void k_gamma128(const float2 *__restrict__ spec, int64_t n_ref,
-                                                  int Q, float2 *__restrict__ gam,
-                                                  float2 *__restrict__ gamx) {
-    const int P2 = Q / 2;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= n_ref * P2 * (kA128Slots + 2)) return;
-    const int slot = (int)(idx % (kA128Slots + 2));
-    const int64_t rp = idx / (kA128Slots + 2);
-    const int p = (int)(rp % P2);
-    const int64_t r = rp / P2;
-    const float2 c = gamma128_coef(spec + r * 65 * (int64_t)Q, Q, p, slot);
-    if (slot < kA128Slots) gam[rp * kA128Slots + slot] = c;
-    else gamx[rp * 2 + (slot - kA128Slots)] = c;
-}
-
 // BF16: the launch's a.bf16, one instance each so that either has its own
 // register allocation.
 template <int NT, bool BF16>
@@ -110,16 +93,11 @@ size_t align128_scratch_bytes(Geo g, int64_t n_ref) {
     return per * (size_t)n_ref;
 }
 
-hipError_t launch_align128(const PairArgs &a, Geo g, const AngleTable &t, float2 *gam,
+hipError_t launch_align128(const PairArgs &a, Geo g, const AngleTable &t, const float2 *gam,
                            hipStream_t s, bool per_wave) {
     const int64_t P = a.pairs ? a.n_pairs : a.n_ref * a.n_img;
     if (P <= 0) return hipSuccess;
-    float2 *gamx = gam + (size_t)a.n_ref * (g.Q / 2) * kA128Slots;
-    const int64_t ng = a.n_ref * (g.Q / 2) * (kA128Slots + 2);
-    hipLaunchKernelGGL(k_gamma128, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, s, a.ref_spec,
-                       a.n_ref, g.Q, gam, gamx);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const float2 *gamx = gam + (size_t)a.n_ref * (g.Q / 2) * kA128Slots;
     if (per_wave) {
         constexpr int NW = 4;  // 38 KiB of LDS: four blocks per compute unit
         hipLaunchKernelGGL((k_align128w<NW>), dim3((unsigned)((P + NW - 1) / NW)), dim3(64 * NW), 0,

@@ -37,6 +37,19 @@ __device__ __forceinline__ int64_t next_work(unsigned long long *counter, int64_
     return *slot;
 }
 
+// What the alignment of an item reads of its reference's table T: the
+// register-FFT coefficients (n = 128 items), else the FP32 spectrum.
+template <int NT>
+__device__ void reference_spectrum(const MixItem &it, const float *T, float2 *lds2) {
+    const int Q = it.Q;
+    float2 *const gam = it.gam, *const spec = it.ref_spec;
+    spectrum_rows<NT>(T, it.n, 0, Q / 2, fft_chunk_rows(it.n, Q), it.d32, lds2,
+                      [&](int p, int w, float2 xe, float2 xo) {
+                          if (gam) store_gamma128(gam, gam + Q / 2 * kA128Slots, p, w, xe, xo);
+                          else store_spectrum(spec, Q, p, w, xe, xo);
+                      });
+}
+
 // Images -> quantile tables for every item of two groups: the work queue
 // holds the images of G0 (the references) first, then those of G1, so that
 // the references, one block each, run beside the first images instead of
@@ -88,16 +101,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         quantile_phase<NT>([&](int k, int b) { return pmf[k * L + b]; }, L, n, Q, it.levels, it.TC,
                            it.d64, Ut, colS, it.qt + gi * (int64_t)Q * n, it.aux + 4 * gi);
         if (G == G0 && it.spec) {
-            // the reference's spectrum, from the table this block just wrote
+            // from the table this block just wrote
             __threadfence_block();
-            spectrum_block<NT>(it.qt + gi * (int64_t)Q * n, n, Q, it.ref_spec, 0, it.d32,
-                               (float2 *)ldsd);
+            reference_spectrum<NT>(it, it.qt + gi * (int64_t)Q * n, (float2 *)ldsd);
         }
     }
 }
 
-// FP32 spectrum of the reference of every item whose reference tables were
-// not computed in this launch (cached references): one block per item.
+// The spectrum or coefficients of the reference of every item whose reference
+// tables were not computed in this launch (cached references): one block per
+// item.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_refspec_mixed(const MixGroup *__restrict__ G) {
     extern __shared__ __align__(16) float2 lds2[];
@@ -105,23 +118,7 @@ __global__ __launch_bounds__(NT) void k_refspec_mixed(const MixGroup *__restrict
     if (i >= G->nitems) return;
     const MixItem &it = G->items[i];
     if (it.count <= 0 || it.spec) return;  // spec: written by the tables kernel
-    spectrum_block<NT>(it.ref_qt, it.n, it.Q, it.ref_spec, 0, it.d32, lds2);
-}
-
-// Register-FFT coefficients of the references of the n = 128 items (after
-// k_refspec_mixed): one block per item.
-__global__ __launch_bounds__(256) void k_gamma_mixed(const MixGroup *__restrict__ G) {
-    const int i = blockIdx.x;
-    if (i >= G->nitems) return;
-    const MixItem &it = G->items[i];
-    if (!it.gam || it.count <= 0) return;
-    const int P2 = it.Q / 2;
-    for (int idx = threadIdx.x; idx < P2 * (kA128Slots + 2); idx += 256) {
-        const int p = idx / (kA128Slots + 2), slot = idx - p * (kA128Slots + 2);
-        const float2 c = gamma128_coef(it.ref_spec, it.Q, p, slot);
-        if (slot < kA128Slots) it.gam[p * kA128Slots + slot] = c;
-        else it.gam[P2 * kA128Slots + 2 * p + (slot - kA128Slots)] = c;
-    }
+    reference_spectrum<NT>(it, it.ref_qt, lds2);
 }
 
 // n = 128 items (work items [0, split)): register-FFT alignment, one image
@@ -315,7 +312,6 @@ hipError_t launch_mixed(const MixGroup *d_refs, const MixGroup *d_imgs, const Mi
                            m.slot_floats, m.region_floats, m.lmax, m.nmax);
     hipLaunchKernelGGL((k_refspec_mixed<NT>), dim3((unsigned)kMaxMix), dim3(NT),
                        sizeof(float2) * (kMaxN + 2 * kFftElems), s, d_imgs);
-    hipLaunchKernelGGL(k_gamma_mixed, dim3((unsigned)kMaxMix), dim3(256), 0, s, d_imgs);
     // four 37 KiB blocks of four waves of the register-FFT kernel per compute unit
     hipLaunchKernelGGL((k_align128_mixed<4>), dim3((unsigned)(2 * grid)), dim3(256), 0, s, d_imgs,
                        counters + 3);

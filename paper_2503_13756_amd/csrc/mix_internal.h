@@ -35,8 +35,9 @@ struct MixItem {
     int mode, bf16, top_k;
     float2 *gam;  // n = 128 register-FFT alignment: coefficients [Q/2][130] of the
                   // reference (written by the launch), or null for the LDS-FFT path
-    int spec;     // reference item: write the FP32 spectrum of its table to ref_spec
-                  // after the tables; image item: its ref_spec is written that way
+    int spec;     // reference item: write the spectrum of its table to ref_spec (its
+                  // coefficients to gam, where set) after the tables; image item: its
+                  // reference's is written that way
     int pad;
 };
 struct MixGroup {

@@ -775,7 +775,7 @@ sw_status run_stack_chunk(Ctx *c, const sw_stack *const *st, int n, int mode, in
         a.count = k.N;
         a.gam = nullptr;
         r.gam = nullptr;
-        a.spec = r.spec = 1;  // the reference item writes the spectrum
+        a.spec = r.spec = 1;  // the reference item writes the spectrum or coefficients
         first += k.N;
         if (i < nfast) split = first;
         gr.items[i] = r;
@@ -816,7 +816,7 @@ sw_status run_stack_chunk(Ctx *c, const sw_stack *const *st, int n, int mode, in
     for (int i = 0; i < n; ++i) {
         gi.items[i].ref_spec = (float2 *)(base + o_spec[i]);
         gr.items[i].ref_spec = gi.items[i].ref_spec;
-        if (i < nfast) gi.items[i].gam = (float2 *)(base + o_gam[i]);
+        if (i < nfast) gr.items[i].gam = gi.items[i].gam = (float2 *)(base + o_gam[i]);
     }
     sw::MixGroup *d_groups = (sw::MixGroup *)(base + o_groups);
     hipError_t e = hipMemcpyAsync(d_groups, hg, 2 * sizeof(sw::MixGroup), hipMemcpyHostToDevice, s);
@@ -1395,7 +1395,9 @@ static sw_status align_batch_impl(void *ctx, const sw_batch *b, sw_result *out, 
     const size_t gam_bytes = fast128 ? sw::align128_scratch_bytes(geo, b->n_ref) : 0;
     void *spec;
     if ((st = take_scratch(spec_bytes + gam_bytes, &spec)) != SW_OK) return st;
-    hipError_t e = sw::launch_spectrum(b->ref_qt, b->n_ref, geo, *t, spec, 0, s);
+    float2 *gam = (float2 *)((char *)spec + spec_bytes);
+    hipError_t e = fast128 ? sw::launch_gamma128(b->ref_qt, b->n_ref, geo, *t, gam, s)
+                           : sw::launch_spectrum(b->ref_qt, b->n_ref, geo, *t, spec, 0, s);
     if (e != hipSuccess) return hip_fail(e, "k_spectrum launch");
     sw::PairArgs a;
     a.ref_qt = b->ref_qt;
@@ -1413,9 +1415,8 @@ static sw_status align_batch_impl(void *ctx, const sw_batch *b, sw_result *out, 
     a.out = (sw::Result *)out;
     a.curve = curve;
     if (fast128) {
-        e = sw::launch_align128(a, geo, *t, (float2 *)((char *)spec + spec_bytes), s,
-                                c->align128_per_wave);
-        if (e != hipSuccess) return hip_fail(e, "k_gamma128 / k_align128 launch");
+        e = sw::launch_align128(a, geo, *t, gam, s, c->align128_per_wave);
+        if (e != hipSuccess) return hip_fail(e, "k_align128 launch");
     } else {
         e = sw::launch_align_pairs(a, geo, *t, s);
         if (e != hipSuccess) return hip_fail(e, "k_align_pairs launch");

@@ -138,13 +138,15 @@ hipError_t launch_align_pairs(const PairArgs &a, Geo g, const AngleTable &t, hip
 // Max-sliced alignment (rotation only) of every pair: n = 64 or 128.
 bool msw_supported(Geo g);
 hipError_t launch_align_msw(const PairArgs &a, Geo g, hipStream_t s);
-// The same for n = 128 with register-resident angle FFTs; needs a coefficient
-// scratch of align128_scratch_bytes() (a.ref_spec must hold the references'
-// FP32 spectra).  per_wave: one pair per wave (k_align128w) instead of one
-// pair per block (k_align128).
+// The same for n = 128 with register-resident angle FFTs, from the references'
+// coefficients (align128_scratch_bytes() of them, written by launch_gamma128
+// from the reference tables; a.ref_spec is not read).  per_wave: one pair per
+// wave (k_align128w) instead of one pair per block (k_align128).
 bool align128_supported(Geo g);
 size_t align128_scratch_bytes(Geo g, int64_t n_ref);
-hipError_t launch_align128(const PairArgs &a, Geo g, const AngleTable &t, float2 *gam,
+hipError_t launch_gamma128(const float *qt, int64_t N, Geo g, const AngleTable &t, float2 *gam,
+                           hipStream_t s);
+hipError_t launch_align128(const PairArgs &a, Geo g, const AngleTable &t, const float2 *gam,
                            hipStream_t s, bool per_wave = true);
 
 // All reference x image pairs on MFMA (bfloat16 spectra, FP32 accumulate),

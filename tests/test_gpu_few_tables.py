@@ -1,0 +1,47 @@
+"""Calls on few images or references, whose work is split over more blocks:
+the splits never change a bit."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def api():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2503_13756_amd import api as A
+
+    return A
+
+
+def dev(x):
+    import torch
+
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+# the packed rows per block of the reference spectra: one (Q/2 <= 512 / refs),
+# several, with a ragged last block, all of them; n = 128 writes coefficients
+@pytest.mark.parametrize("L,n,Q", [(24, 24, 20), (40, 48, 52), (32, 128, 36), (64, 256, 8)])
+@pytest.mark.parametrize("refs", [1, 37, 130, 520])
+def test_reference_spectra_row_split(api, L, n, Q, refs):
+    _, imgs = synth.make_raw_stack(31 + L, L, 6)
+    ctx = api.Context(0)
+    q, a = api.tables(ctx, dev(imgs), n, Q)
+    rep = (refs + 5) // 6
+    rq = q.repeat(rep, 1, 1)[:refs].contiguous()
+    ra = a.repeat(rep, 1)[:refs].contiguous()
+    res, curve = api.align_batch(ctx, rq, ra, q[:2].contiguous(), a[:2].contiguous(), L,
+                                 want_curve=True)
+    res, curve = res.cpu().numpy(), curve.cpu().numpy()
+    for r in range(min(6, refs)):
+        one, c1 = api.align_batch(ctx, rq[r:r + 1].contiguous(), ra[r:r + 1].contiguous(),
+                                  q[:2].contiguous(), a[:2].contiguous(), L, want_curve=True)
+        for k in range(r, refs, 6):
+            assert np.array_equal(res[2 * k:2 * k + 2], one.cpu().numpy()), (r, k)
+            assert np.array_equal(curve[2 * k:2 * k + 2], c1.cpu().numpy()), (r, k)
+    ctx.close()
