@@ -89,22 +89,37 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     }
 }
 
-// Small batches: one block per (image, task group), so that a single image
-// spreads over many compute units.  Every block stages the whole image.
-template <int NT>
-__global__ __launch_bounds__(NT) void k_project_split(const float *__restrict__ img, int64_t N,
-                                                      ProjShape P, const float2 *__restrict__ dtab,
-                                                      float *__restrict__ pmf) {
+// Small batches: one block per (image, group of eight tasks, one task per
+// wave), so that a single image spreads over several compute units.  Every
+// block stages the whole image, in four-kind strips of R rows: what bounds a
+// block is latency (the loads of a strip, its staging and the chain of a
+// task's rows, with two waves per SIMD), so the block has as many threads to
+// stage with as the strips allow, and few, tall strips.  One image (against
+// 128-thread blocks of two tasks on 64 KiB of sliding windows): 18 -> 10 us at
+// L = 64, 46 -> 19 at 128, 162 -> 43 at 256.  Bitwise the sums of the other
+// kernels.
+template <int NT, int KP>
+__global__ __launch_bounds__(NT) void k_project_few(const float *__restrict__ img, int64_t N,
+                                                    ProjShape P, const float2 *__restrict__ dtab,
+                                                    float *__restrict__ pmf, int R,
+                                                    int strip_floats) {
+    constexpr int NW = NT / 64;
     extern __shared__ __align__(16) float lds[];
     const int64_t g = blockIdx.x;
     if (g >= N) return;
-    const float *F = img + g * (int64_t)P.L * P.L;
-    float *out = pmf + g * (int64_t)P.n * P.L;
-    int bad = 0;
-    project_group<NT, 1>(F, P, dtab, lds, (int)blockIdx.y * (NT / 64), bad,
-                         [&](int k, int b, float v) { out[k * P.L + b] = v; });
-    if (bad && blockIdx.y == 0)
-        for (int t = threadIdx.x; t < P.n * P.L; t += NT) out[t] = __int_as_float(0x7fc00000);
+    const int L = P.L, n = P.n, tg0 = (int)blockIdx.y * NW;
+    const float *const F[1] = {img + g * (int64_t)L * L};
+    float *out = pmf + g * (int64_t)n * L;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float acc[1][1][4];
+    int bad[1];
+    project_images2<NT, 1, 1, KP>(F, 1, P, dtab, lds, (float4 *)(lds + strip_floats), R, tg0, acc,
+                                  bad);
+    if (!bad[0])
+        emit_outputs<1>(P, tg0, wave, NW, lane, acc[0],
+                        [&](int k, int b, float v) { out[k * L + b] = v; });
+    else if (blockIdx.y == 0)
+        for (int t = threadIdx.x; t < n * L; t += NT) out[t] = __int_as_float(0x7fc00000);
 }
 
 template <int NT, int TPW>
@@ -133,6 +148,44 @@ static hipError_t launch_project2_t(const float *img, int64_t N, const ProjShape
     return hipGetLastError();
 }
 
+// Strips of up to 140 KiB (one block per compute unit) while every block has
+// a unit of its own, else of 64 KiB (two).  KP staging passes, the fewest that
+// cover the strip's rows.
+template <int NT, int KP>
+static hipError_t launch_project_few_t(const float *img, int64_t N, const ProjShape &P, int R,
+                                       const float2 *dtab, float *pmf, hipStream_t s) {
+    static const hipError_t attr = hipFuncSetAttribute(
+        (const void *)k_project_few<NT, KP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        152 * 1024);
+    (void)attr;
+    const int strip_floats = 4 * R * s4_positions(P.L);
+    const size_t lds = sizeof(float) * strip_floats + sizeof(float4) * (P.slots + 1);
+    const int groups = (P.ntasks + NT / 64 - 1) / (NT / 64);
+    hipLaunchKernelGGL((k_project_few<NT, KP>), dim3((unsigned)N, (unsigned)groups), dim3(NT), lds,
+                       s, img, N, P, dtab, pmf, R, strip_floats);
+    return hipGetLastError();
+}
+
+static hipError_t launch_project_few(const float *img, int64_t N, const ProjShape &P,
+                                     const float2 *dtab, float *pmf, hipStream_t s) {
+    constexpr int NT = 512;
+    static const int cus = [] {
+        int dev = 0, c = 0;
+        (void)hipGetDevice(&dev);
+        (void)hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev);
+        return c > 0 ? c : 256;
+    }();
+    const int groups = (P.ntasks + NT / 64 - 1) / (NT / 64);
+    const int bytes = N * groups <= cus ? 140 * 1024 : 64 * 1024;
+    const int most = s4_rows<NT, 8>(P.L, bytes), strips = (P.L + most - 1) / most;
+    const int R = (P.L + strips - 1) / strips;  // <= most: strips of nearly equal height
+    if (s4_rows<NT, 2>(P.L, bytes) >= R)
+        return launch_project_few_t<NT, 2>(img, N, P, R, dtab, pmf, s);
+    if (s4_rows<NT, 4>(P.L, bytes) >= R)
+        return launch_project_few_t<NT, 4>(img, N, P, R, dtab, pmf, s);
+    return launch_project_few_t<NT, 8>(img, N, P, R, dtab, pmf, s);
+}
+
 hipError_t launch_project(const float *img, int64_t N, Geo g, const AngleTable &t,
                           const ProjPlan &pp, float *pmf, hipStream_t s, bool split) {
     if (N <= 0) return hipSuccess;
@@ -140,18 +193,7 @@ hipError_t launch_project(const float *img, int64_t N, Geo g, const AngleTable &
     if (pp.L != g.L || pp.n != g.n || pp.ntasks != P.ntasks) return hipErrorInvalidValue;
     P.perm = pp.perm;
     P.trow = pp.trow;
-    if (split) {
-        constexpr int NT = 128;
-        const int groups = (P.ntasks + NT / 64 - 1) / (NT / 64);
-        const size_t lds = sizeof(float) * kStripFloats;
-        static const hipError_t attr = hipFuncSetAttribute(
-            (const void *)k_project_split<NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-            96 * 1024);
-        (void)attr;
-        hipLaunchKernelGGL((k_project_split<NT>), dim3((unsigned)N, (unsigned)groups), dim3(NT),
-                           lds, s, img, N, P, t.d32, pmf);
-        return hipGetLastError();
-    }
+    if (split) return launch_project_few(img, N, P, t.d32, pmf, s);
     const int w512 = tasks_per_wave(P.ntasks, 512);
     if (s4_supported(g.L)) {  // two images per block where all tasks fit one group of six
         const int64_t table = (int64_t)g.n * g.L;  // room to park the second image's sums
