@@ -278,6 +278,25 @@ __host__ __device__ inline QuantMode quant_mode_for(int L) {
     return L <= 128 ? kQuantHalf : kQuantWave;
 }
 
+// The scalars of one image (or signed part) from its column sums colS [n][2]
+// (sum of quantiles, sum of squares), by one wave in a fixed order: E and the
+// translation moment a in out[0..2], on every lane.
+__device__ __forceinline__ void column_aux(const double *colS, int n, int Q,
+                                           const double2 *__restrict__ d64, int lane,
+                                           double (&out)[3]) {
+    double e = 0.0, x = 0.0, y = 0.0;
+    for (int k = lane; k < n; k += 64) {
+        const double qbar = colS[2 * k] / (double)Q;
+        const double2 d = d64[k];
+        e += colS[2 * k + 1];
+        x += qbar * d.x;
+        y += qbar * d.y;
+    }
+    out[0] = wave_sum_d(e);
+    out[1] = wave_sum_d(x) / (double)n;
+    out[2] = wave_sum_d(y) / (double)n;
+}
+
 // The whole CDF/quantile phase of one image, shared by the stand-alone,
 // fused and mixed kernels.  col(k, b) reads bin b of column k.  LDS: Ut
 // (Q * (TC + 1) floats), colS (2 n doubles).
@@ -294,22 +313,13 @@ __device__ void quantile_phase(ColFn col, int L, int n, int Q, int levels, int T
     else
         mass0 = quantile_tiles<NT, false>(col, L, n, Q, levels, TC, Ut, colS, U);
     if (wave == 0) {
-        double e = 0.0, x = 0.0, y = 0.0;
-        for (int k = lane; k < n; k += 64) {
-            const double qbar = colS[2 * k] / (double)Q;
-            const double2 d = d64[k];
-            e += colS[2 * k + 1];
-            x += qbar * d.x;
-            y += qbar * d.y;
-        }
-        e = wave_sum_d(e);
-        x = wave_sum_d(x);
-        y = wave_sum_d(y);
+        double s[3];
+        column_aux(colS, n, Q, d64, lane, s);
         if (lane == 0 && A) {
             A[0] = mass0;  // column 0 is inverted by wave 0
-            A[1] = e;
-            A[2] = x / (double)n;
-            A[3] = y / (double)n;
+            A[1] = s[0];
+            A[2] = s[1];
+            A[3] = s[2];
         }
     }
     __syncthreads();

@@ -1032,15 +1032,19 @@ sw_status sw_tables(void *ctx, const float *img, int64_t N, const sw_geom *g, fl
     int64_t chunk = (int64_t)((size_t)256 << 20) / (int64_t)per;
     if (chunk < 1) chunk = 1;
     if (chunk > N) chunk = N;
+    // a small batch's column sums follow the projections
+    const size_t pmf_bytes = (per * (size_t)chunk + 255) & ~(size_t)255;
+    const size_t cols_bytes = small ? sw::quantile_cols_bytes(chunk, geo.n, 1) : 0;
     void *pmf;
-    if ((st = get_scratch(c, per * (size_t)chunk, s, &pmf)) != SW_OK) return st;
+    if ((st = get_scratch(c, pmf_bytes + cols_bytes, s, &pmf)) != SW_OK) return st;
+    double *cols = small ? (double *)((char *)pmf + pmf_bytes) : nullptr;
     for (int64_t i0 = 0; i0 < N; i0 += chunk) {
         const int64_t m = N - i0 < chunk ? N - i0 : chunk;
         hipError_t e = sw::launch_project(img + i0 * (int64_t)geo.L * geo.L, m, geo, *t, *pp,
                                           (float *)pmf, s, small);
         if (e != hipSuccess) return hip_fail(e, "k_project launch");
         e = sw::launch_quantiles((const float *)pmf, m, geo, *t, qt + i0 * (int64_t)geo.Q * geo.n,
-                                 aux ? aux + 4 * i0 : nullptr, s, small);
+                                 aux ? aux + 4 * i0 : nullptr, s, small, cols);
         if (e != hipSuccess) return hip_fail(e, "k_quantile launch");
     }
     return SW_OK;
@@ -1116,8 +1120,12 @@ sw_status sw_tables_rf(void *ctx, const float *img, int64_t N, const sw_geom *g,
     int64_t chunk = (int64_t)((size_t)256 << 20) / (int64_t)per;
     if (chunk < 1) chunk = 1;
     if (chunk > N) chunk = N;
+    // a small batch's column sums follow the projections
+    const size_t pmf_bytes = (per * (size_t)chunk + 255) & ~(size_t)255;
+    const size_t cols_bytes = small ? sw::quantile_cols_bytes(chunk, geo.n, 2) : 0;
     void *pmf;
-    if ((st = get_scratch(c, per * (size_t)chunk, s, &pmf)) != SW_OK) return st;
+    if ((st = get_scratch(c, pmf_bytes + cols_bytes, s, &pmf)) != SW_OK) return st;
+    double *cols = small ? (double *)((char *)pmf + pmf_bytes) : nullptr;
     for (int64_t i0 = 0; i0 < N; i0 += chunk) {
         const int64_t m = N - i0 < chunk ? N - i0 : chunk;
         hipError_t e = sw::launch_project(img + i0 * (int64_t)geo.L * geo.L, m, geo, *t, *pp,
@@ -1127,7 +1135,7 @@ sw_status sw_tables_rf(void *ctx, const float *img, int64_t N, const sw_geom *g,
         if (e != hipSuccess) return hip_fail(e, "k_ramp launch");
         e = sw::launch_quantiles_rf((const float *)pmf, m, geo, *t,
                                     qt + i0 * (int64_t)2 * geo.Q * geo.n,
-                                    aux ? aux + 4 * i0 : nullptr, s, small);
+                                    aux ? aux + 4 * i0 : nullptr, s, small, cols);
         if (e != hipSuccess) return hip_fail(e, "k_quantile_rf launch");
     }
     return SW_OK;
@@ -1234,19 +1242,23 @@ static sw_status tables_fourier(void *ctx, const float *img, int64_t N, const sw
     if (chunk < 1) chunk = 1;
     if (chunk > N) chunk = N;
     const size_t pmf_bytes = (per * (size_t)chunk + 255) & ~(size_t)255;
+    const size_t slot_bytes =
+        (sw::fourier_slot_bytes(S.L, S.Nf) * slots + 255) & ~(size_t)255;
+    // after the slots, the column sums of the largest chunk that is a small batch
+    const int64_t few = c->small(chunk) ? chunk : c->small(N % chunk) ? N % chunk : 0;
+    const size_t cols_bytes = sw::quantile_cols_bytes(few, geo.n, 1);
     void *scr;
-    if ((st = get_scratch(c, pmf_bytes + sw::fourier_slot_bytes(S.L, S.Nf) * slots, s, &scr)) !=
-        SW_OK)
-        return st;
+    if ((st = get_scratch(c, pmf_bytes + slot_bytes + cols_bytes, s, &scr)) != SW_OK) return st;
     float *pmf = (float *)scr;
     void *slot_mem = (char *)scr + pmf_bytes;
+    double *cols = (double *)((char *)scr + pmf_bytes + slot_bytes);
     for (int64_t i0 = 0; i0 < N; i0 += chunk) {
         const int64_t m = N - i0 < chunk ? N - i0 : chunk;
         hipError_t e = sw::launch_fourier(img + i0 * (int64_t)geo.L * geo.L, m, S, T, slot_mem,
                                           slots, pmf, s);
         if (e != hipSuccess) return hip_fail(e, "k_fourier launch");
         e = sw::launch_quantiles(pmf, m, geo, *dirs, qt + i0 * (int64_t)geo.Q * geo.n,
-                                 aux ? aux + 4 * i0 : nullptr, s, c->small(m));
+                                 aux ? aux + 4 * i0 : nullptr, s, c->small(m), cols);
         if (e != hipSuccess) return hip_fail(e, "k_quantile launch");
     }
     return SW_OK;

@@ -86,12 +86,18 @@ static_assert(sizeof(Result) == 24, "sw_result is 24 bytes");
 // device with one block per image
 hipError_t launch_project(const float *img, int64_t N, Geo g, const AngleTable &t,
                           const ProjPlan &pp, float *pmf, hipStream_t s, bool split = false);
+// small: for batches too small to fill the device with one block per image;
+// cols: scratch of quantile_cols_bytes() (one part, or two for the signed
+// parts) for the launches that take many blocks per image, or null
+size_t quantile_cols_bytes(int64_t N, int n, int parts);
 hipError_t launch_quantiles(const float *pmf, int64_t N, Geo g, const AngleTable &t, float *qt,
-                            double *aux, hipStream_t s, bool small = false);
+                            double *aux, hipStream_t s, bool small = false,
+                            double *cols = nullptr);
 // Ramp-filtered projections: the stacked [2Q][n] tables of the positive and
 // negative parts (per image) from signed [n][L] columns.
 hipError_t launch_quantiles_rf(const float *pf, int64_t N, Geo g, const AngleTable &t, float *qt,
-                               double *aux, hipStream_t s, bool small = false);
+                               double *aux, hipStream_t s, bool small = false,
+                               double *cols = nullptr);
 // Ramp filter of C columns of L bins (src may equal dst).  hx: the filter's
 // cyclic kernel as a table of 2 LP - 1 floats, hx[t] = h[t - (LP - 1)] for
 // |t - (LP - 1)| < L and 0 otherwise, LP = ramp_padded_length(L).

@@ -45,3 +45,36 @@ def test_reference_spectra_row_split(api, L, n, Q, refs):
             assert np.array_equal(res[2 * k:2 * k + 2], one.cpu().numpy()), (r, k)
             assert np.array_equal(curve[2 * k:2 * k + 2], c1.cpu().numpy()), (r, k)
     ctx.close()
+
+
+# images per launch: one, several, one below and at the default small-batch
+# limit of a 256-unit device; sides with one strip, with several, at the edges
+# of the staging; columns by half waves (L <= 128) and by whole waves
+@pytest.mark.parametrize("L,n,Q", [(8, 8, 8), (39, 48, 48), (97, 24, 20), (128, 128, 128),
+                                   (129, 96, 60), (256, 72, 256)])
+@pytest.mark.parametrize("N", [1, 5, 255])
+def test_small_batches_equal_large_ones(api, tmp_path, L, n, Q, N):
+    """The launches of a small batch (several blocks per image) against those of
+    a large one (one or two images per block): tables and aux, plain and
+    ramp-filtered, bit for bit, with a NaN image, an empty one and an infinite
+    pixel among them."""
+    paths = {}
+    for name, lim in (("small", 1 << 30), ("large", 0)):
+        paths[name] = tmp_path / f"{name}.json"
+        paths[name].write_text('{"small_batch": %d}' % lim)
+    _, imgs = synth.make_raw_stack(77 + L, L, min(N, 5))
+    imgs = np.concatenate([imgs] * ((N + 4) // 5))[:N].copy()
+    if N >= 5:
+        imgs[1, L // 2, L // 2] = np.nan
+        imgs[2] = 0.0
+        imgs[3, L // 2, L // 3] = np.inf
+    x = dev(imgs)
+    for ramp in (False, True):
+        out = {}
+        for name, p in paths.items():
+            ctx = api.Context(0, tune_json=str(p))
+            q, a = api.tables(ctx, x, n, Q, ramp=ramp)
+            out[name] = (q.cpu().numpy().view(np.uint32), a.cpu().numpy().view(np.uint64))
+            ctx.close()
+        assert np.array_equal(out["small"][0], out["large"][0]), ramp
+        assert np.array_equal(out["small"][1], out["large"][1]), ramp
