@@ -79,11 +79,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         ProjShape P;
         P.L = it.L;
         P.n = it.n;
-        P.S = strip_stride(it.L);
-        P.RS = strip_row_floats(it.L);
-        P.R = it.R;  // rows of the four-kind strips (plan_mixed clamps it)
         P.slots = it.n / 8 + 1;
-        P.items = P.slots * it.L;
         P.ntasks = proj_ntasks(it.L, it.n);
         P.perm = it.perm;
         P.trow = it.trow;
@@ -92,7 +88,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         const float *F = it.img + gi * (int64_t)L * L;
         int bad = 0;
         // the slot table sits in the column-sum area until the quantile phase
-        project_image4<NT, TPW>(F, P, it.d32, region, (float4 *)colS, P.R, bad,
+        const int R = it.R;  // rows of the strips (plan_mixed clamps it)
+        project_image4<NT, TPW>(F, P, it.d32, region, (float4 *)colS, R, bad,
                                 [&](int k, int b, float v) { pmf[k * L + b] = v; });
         if (bad)
             for (int t = threadIdx.x; t < n * L; t += NT) pmf[t] = __int_as_float(0x7fc00000);

@@ -5,6 +5,29 @@
 
 namespace sw {
 
+__global__ __launch_bounds__(256) void k_plan_lanes(PlanLane *lanes, int count, int L) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= count) return;
+    const PlanLane p = lanes[i];
+    float A3 = -100.f, A3n = -100.f;  // no item: clamps to the zero padding
+    if (p.item >= 0) {
+        const float c = p.A3, s = -p.A3n, r = s / c;
+        const int b = p.item - p.slot * L;
+        const double c0 = 0.5 * (double)(L - 1), ic = 1.0 / (double)c;
+        const double a3 = ((double)b - c0 - 1.0) * ic + c0 + 3.0 - c0 * (double)r;
+        A3 = (float)a3;
+        A3n = (float)(a3 + (double)r);
+    }
+    lanes[i].A3 = A3;
+    lanes[i].A3n = A3n;
+}
+
+hipError_t launch_plan_lanes(PlanLane *lanes, int count, int L, hipStream_t s) {
+    hipLaunchKernelGGL(k_plan_lanes, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, lanes,
+                       count, L);
+    return hipGetLastError();
+}
+
 template <int NT, int TPW>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kProjMinWaves<NT, TPW>, NT <= 256 ? 2 : 4))) void k_project(const float *__restrict__ img, int64_t N,
                                                 ProjShape P, const float2 *__restrict__ dtab,
@@ -15,15 +38,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kProjMinWave
     const float *F = img + g * (int64_t)P.L * P.L;
     float *out = pmf + g * (int64_t)P.n * P.L;
     int bad = 0;
-    if constexpr (NT == 512) {  // four-kind strips, the slot table after them
-        // (an opaque offset: a constant one trips the compiler's LDS cast)
-        int off = kStripFloats;
-        asm volatile("" : "+s"(off));
-        project_image4<NT, TPW>(F, P, dtab, lds, (float4 *)(lds + off), strip4_rows_max(P.L), bad,
-                                [&](int k, int b, float v) { out[k * P.L + b] = v; });
-    } else
-        project_image<NT, TPW>(F, P, dtab, lds, bad,
-                               [&](int k, int b, float v) { out[k * P.L + b] = v; });
+    // four-kind strips, the slot table after them (an opaque offset: a constant
+    // one trips the compiler's LDS cast)
+    int off = kStripFloats;
+    asm volatile("" : "+s"(off));
+    project_image4<NT, TPW>(F, P, dtab, lds, (float4 *)(lds + off), strip4_rows_max(P.L), bad,
+                            [&](int k, int b, float v) { out[k * P.L + b] = v; });
     if (bad) {
         // an image with a non-finite value gets an all-NaN projection
         __syncthreads();
@@ -122,6 +142,54 @@ __global__ __launch_bounds__(NT) void k_project_few(const float *__restrict__ im
         for (int t = threadIdx.x; t < n * L; t += NT) out[t] = __int_as_float(0x7fc00000);
 }
 
+// Two images per block for geometries of more tasks than the kernels above
+// hold at once (more than 72; L = n = 256 has 132): 1024 threads and strips of
+// 70 KiB per image, one block per compute unit, five tasks per wave, in as
+// many groups as it takes (each stages the images again).  The accumulation is
+// bound by the VALU: sharing the weights between two images takes it from
+// 21.5 to 16.75 instructions per row and image, and the four-kind strips from
+// four LDS reads per row to three.  1,500 images at L = n = 256 2.31 -> 1.61
+// ms against the one-image kernel on sliding windows (nine tasks per wave);
+// all tasks in one group, with nine per wave, or eleven of 768 threads, spill:
+// 1.64-1.87 ms.  Bitwise the projections of k_project.
+constexpr int kImg2BytesLarge = 70 * 1024;
+
+template <int NT, int TPW>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_project2_large(
+    const float *__restrict__ img, int64_t N, ProjShape P, const float2 *__restrict__ dtab,
+    float *__restrict__ pmf) {
+    constexpr int IB = kImg2BytesLarge;
+    constexpr int NW = NT / 64;
+    extern __shared__ __align__(16) float lds[];
+    const int64_t g0 = 2 * (int64_t)blockIdx.x;
+    if (g0 >= N) return;
+    const int nimg = N - g0 >= 2 ? 2 : 1;
+    const int L = P.L, n = P.n;
+    const float *F[2] = {img + g0 * (int64_t)L * L, img + (g0 + nimg - 1) * (int64_t)L * L};
+    // the slot table after both images' strips (an opaque offset, as above)
+    int off = 2 * (IB / 4);
+    asm volatile("" : "+s"(off));
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int tg0 = 0; tg0 < P.ntasks; tg0 += NW * TPW) {
+        float acc[2][TPW][4];
+        int bad[2];
+        project_images2<NT, TPW, 2, 2, IB>(F, nimg, P, dtab, lds, (float4 *)(lds + off),
+                                           s4_rows<NT>(L, IB), tg0, acc, bad);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            if (g < nimg) {  // block-uniform
+                float *out = pmf + (g0 + g) * (int64_t)n * L;
+                if (!bad[g])
+                    emit_outputs<TPW>(P, tg0, wave, NW, lane, acc[g],
+                                      [&](int k, int b, float v) { out[k * L + b] = v; });
+                else if (tg0 == 0)  // an image with a non-finite value: all NaN
+                    for (int t = threadIdx.x; t < n * L; t += NT)
+                        out[t] = __int_as_float(0x7fc00000);
+            }
+        }
+    }
+}
+
 template <int NT, int TPW>
 static hipError_t launch_project_t(const float *img, int64_t N, const ProjShape &P,
                                    const float2 *dtab, float *pmf, hipStream_t s) {
@@ -186,6 +254,19 @@ static hipError_t launch_project_few(const float *img, int64_t N, const ProjShap
     return launch_project_few_t<NT, 8>(img, N, P, R, dtab, pmf, s);
 }
 
+template <int NT, int TPW>
+static hipError_t launch_project2_large(const float *img, int64_t N, const ProjShape &P,
+                                        const float2 *dtab, float *pmf, hipStream_t s) {
+    const size_t lds = 2 * (size_t)kImg2BytesLarge + sizeof(float4) * (P.slots + 1);
+    static const hipError_t attr = hipFuncSetAttribute(
+        (const void *)k_project2_large<NT, TPW>,
+        hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+    (void)attr;
+    hipLaunchKernelGGL((k_project2_large<NT, TPW>), dim3((unsigned)((N + 1) / 2)), dim3(NT), lds, s,
+                       img, N, P, dtab, pmf);
+    return hipGetLastError();
+}
+
 hipError_t launch_project(const float *img, int64_t N, Geo g, const AngleTable &t,
                           const ProjPlan &pp, float *pmf, hipStream_t s, bool split) {
     if (N <= 0) return hipSuccess;
@@ -209,11 +290,7 @@ hipError_t launch_project(const float *img, int64_t N, Geo g, const AngleTable &
     if (w512 <= 5) return launch_project_t<512, 5>(img, N, P, t.d32, pmf, s);
     if (w512 <= 6) return launch_project_t<512, 6>(img, N, P, t.d32, pmf, s);
     if (w512 <= 9) return launch_project_t<512, 9>(img, N, P, t.d32, pmf, s);
-    const int w1024 = tasks_per_wave(P.ntasks, 1024);
-    if (w1024 <= 9) return launch_project_t<1024, 9>(img, N, P, t.d32, pmf, s);
-    if (w1024 <= 12) return launch_project_t<1024, 12>(img, N, P, t.d32, pmf, s);
-    // larger task counts run in several task groups
-    return launch_project_t<1024, 12>(img, N, P, t.d32, pmf, s);
+    return launch_project2_large<1024, 5>(img, N, P, t.d32, pmf, s);
 }
 
 }  // namespace sw

@@ -1,11 +1,12 @@
 // Fused projection + CDF/quantile stage: one block turns one image (two, in
 // k_tables2) into its quantile table without the projection leaving the
 // chip.  The projection accumulates in registers across LDS image strips
-// (the four-kind strips of proj2_dev.h for 512-thread blocks, the
-// sliding-window strips of proj_dev.h for 256 threads); after the last strip
+// (the four-kind strips of proj2_dev.h); after the last strip
 // the block writes the PMF table into the same LDS region and inverts its
 // columns there (quant_dev.h).  Results are bitwise those of the stand-alone
 // projection followed by the stand-alone quantile stage.
+#include <algorithm>
+
 #include "proj2_dev.h"
 #include "proj_dev.h"
 #include "quant_dev.h"
@@ -20,7 +21,7 @@ struct TablesShape {
 };
 
 template <int NT, int TPW>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kProjMinWaves<NT, TPW>, NT <= 256 ? 2 : 4))) void k_tables(const float *__restrict__ img, int64_t N,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kProjMinWaves<NT, TPW>, 4))) void k_tables(const float *__restrict__ img, int64_t N,
                                                TablesShape T, const float2 *__restrict__ d32,
                                                const double2 *__restrict__ d64,
                                                float *__restrict__ qt, double *__restrict__ aux) {
@@ -35,12 +36,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kProjMinWave
     float *Ut = (float *)(colS + 2 * n);
     const float *F = img + g * (int64_t)L * L;
     int bad = 0;
-    if constexpr (NT == 512)  // four-kind strips; the slot table in the column-sum area
-        project_image4<NT, TPW>(F, P, d32, region, (float4 *)colS, strip4_rows_max(L), bad,
-                                [&](int k, int b, float v) { region[k * L + b] = v; });
-    else
-        project_image<NT, TPW>(F, P, d32, region, bad,
-                               [&](int k, int b, float v) { region[k * L + b] = v; });
+    // the slot table in the column-sum area
+    project_image4<NT, TPW>(F, P, d32, region, (float4 *)colS, strip4_rows_max(L), bad,
+                            [&](int k, int b, float v) { region[k * L + b] = v; });
     if (bad)
         for (int t = threadIdx.x; t < n * L; t += NT) region[t] = __int_as_float(0x7fc00000);
     __syncthreads();
@@ -279,30 +277,33 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     }
 }
 
-// Bytes of LDS the fused kernel needs for a geometry (0 when it cannot run),
-// with a strip region of at least min_region floats.
-size_t tables_lds_bytes(Geo g, int nt, TablesShape *out, int min_region = 0) {
+// Bytes of LDS the fused kernels need for a geometry within `budget` (0 when
+// they cannot run), with a strip region of at least min_region floats.  All
+// tasks run in one group of `tasks` per wave at most: the PMF table is written
+// over the strip buffers.
+static size_t tables_lds_bytes(Geo g, int nt, int tasks, size_t budget, TablesShape *out,
+                               int min_region = kStripFloats) {
     TablesShape T;
     T.P = proj_shape(g.L, g.n);
     T.Q = g.Q;
     T.levels = g.levels;
-    // all tasks in one group: the PMF table is written over the strip buffers
-    if (tasks_per_wave(T.P.ntasks, nt) > (nt >= 512 ? 9 : 20)) return 0;
-    int region = kStripFloats > min_region ? kStripFloats : min_region;
-    if (region < g.n * g.L) region = g.n * g.L;
-    region = (region + 1) & ~1;
+    if (tasks_per_wave(T.P.ntasks, nt) > tasks) return 0;
+    const int region = (std::max(min_region, g.n * g.L) + 1) & ~1;
     T.region_floats = region;
     const size_t fixed = sizeof(float) * region + sizeof(double) * 2 * g.n;
-    // two blocks per CU when the PMF table allows it (160 KiB of LDS per CU)
-    const size_t budget2 = 79 * 1024, budget1 = 150 * 1024;
-    const size_t budget = fixed + sizeof(float) * g.Q * 9 <= budget2 ? budget2 : budget1;
     if (fixed + sizeof(float) * g.Q * 9 > budget) return 0;
     T.TC = pick_tc(g.n, g.Q, budget - fixed);
     if (out) *out = T;
     return fixed + sizeof(float) * g.Q * (T.TC + 1);
 }
+// Two 512-thread blocks per compute unit (160 KiB of LDS), or one of 1024
+// threads where the PMF table is larger (L beyond about 128 at n = L).
+constexpr size_t kTablesLds2 = 79 * 1024, kTablesLds1 = 150 * 1024, kTablesLds1Most = 158 * 1024;
+constexpr int kTablesImg1Bytes = 64 * 1024;  // strips of each of two images, one block per unit
 
-bool tables_fused_fits(Geo g) { return tables_lds_bytes(g, 256, nullptr) != 0; }
+bool tables_fused_fits(Geo g) {
+    return tables_lds_bytes(g, 1024, 5, kTablesLds1, nullptr) != 0;
+}
 
 template <int NT, int TPW>
 static hipError_t launch_tables_t(const float *img, int64_t N, const TablesShape &T, size_t lds,
@@ -320,7 +321,7 @@ static hipError_t launch_tables2_q(const float *img, int64_t N, const TablesShap
                                    const AngleTable &t, float *qt, double *aux, hipStream_t s) {
     static const hipError_t attr = hipFuncSetAttribute((const void *)k_tables2<NT, TPW, QM, IB>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       152 * 1024);
+                                                       kTablesLds1Most);
     (void)attr;
     hipLaunchKernelGGL((k_tables2<NT, TPW, QM, IB>), dim3((unsigned)((N + 1) / 2)), dim3(NT), lds,
                        s, img, N, T, t.d32, t.d64, qt, aux);
@@ -359,21 +360,22 @@ hipError_t launch_tables(const float *img, int64_t N, Geo g, const AngleTable &t
                          int per_block) {
     if (N <= 0) return hipSuccess;
     TablesShape T;
-    size_t lds = tables_lds_bytes(g, 512, &T);
+    const size_t lds = tables_lds_bytes(g, 512, 9, kTablesLds2, &T);
     if (pp.L != g.L || pp.n != g.n || pp.ntasks != proj_ntasks(g.L, g.n))
         return hipErrorInvalidValue;
     T.P.perm = pp.perm;
     T.P.trow = pp.trow;
-    if (lds != 0 && lds <= 79 * 1024) {
+    if (lds != 0) {
         const int w = tasks_per_wave(T.P.ntasks, 512);
         if (per_block == 2 && s4_supported(g.L)) {
             // two images' strips a little over 32 KiB apart (one more strip
             // row at L = 128) while the block still fits two per CU and the
             // quantile phase keeps its column tile
             TablesShape T2;
-            const size_t lds2 = tables_lds_bytes(g, 512, &T2, 2 * kImg2BytesWide / 4);
+            const size_t lds2 =
+                tables_lds_bytes(g, 512, 9, kTablesLds2, &T2, 2 * kImg2BytesWide / 4);
             hipError_t e = hipSuccess;
-            if (lds2 != 0 && lds2 <= 79 * 1024 && T2.TC >= T.TC) {
+            if (lds2 != 0 && T2.TC >= T.TC) {
                 T2.P.perm = pp.perm;
                 T2.P.trow = pp.trow;
                 if (launch_tables2_w<kImg2BytesWide>(img, N, g, T2, lds2, w, t, qt, aux, s, &e))
@@ -389,15 +391,25 @@ hipError_t launch_tables(const float *img, int64_t N, Geo g, const AngleTable &t
         if (w <= 6) return launch_tables_t<512, 6>(img, N, T, lds, t, qt, aux, s);
         if (w <= 9) return launch_tables_t<512, 9>(img, N, T, lds, t, qt, aux, s);
     }
-    lds = tables_lds_bytes(g, 256, &T);
-    if (lds == 0) return hipErrorInvalidValue;  // caller checks tables_fused_fits first
-    T.P.perm = pp.perm;
-    T.P.trow = pp.trow;
-    const int tpw = tasks_per_wave(T.P.ntasks, 256);
-    if (tpw <= 4) return launch_tables_t<256, 4>(img, N, T, lds, t, qt, aux, s);
-    if (tpw <= 8) return launch_tables_t<256, 8>(img, N, T, lds, t, qt, aux, s);
-    if (tpw <= 12) return launch_tables_t<256, 12>(img, N, T, lds, t, qt, aux, s);
-    return launch_tables_t<256, 20>(img, N, T, lds, t, qt, aux, s);
+    // One block per compute unit: 16 waves, two images per block where the
+    // second image's sums can wait in its table.  (A 256-thread block on
+    // sliding windows did this with four waves: 4,000 images at L = n = Q = 144
+    // 2.84 ms, now 1.22.)
+    TablesShape T1;
+    if (tables_lds_bytes(g, 1024, 5, kTablesLds1, &T1) == 0)
+        return hipErrorInvalidValue;  // caller checks tables_fused_fits first
+    if (per_block == 2 && (int64_t)g.Q * g.n >= kParkFloats<1024, 5>) {
+        const size_t lds2 =
+            tables_lds_bytes(g, 1024, 5, kTablesLds1Most, &T1, 2 * kTablesImg1Bytes / 4);
+        if (lds2 == 0) return hipErrorInvalidValue;  // fits whenever the one-image form does
+        T1.P.perm = pp.perm;
+        T1.P.trow = pp.trow;
+        return launch_tables2_t<1024, 5, kTablesImg1Bytes>(img, N, T1, lds2, t, qt, aux, s);
+    }
+    const size_t lds1 = tables_lds_bytes(g, 1024, 5, kTablesLds1, &T1);
+    T1.P.perm = pp.perm;
+    T1.P.trow = pp.trow;
+    return launch_tables_t<1024, 5>(img, N, T1, lds1, t, qt, aux, s);
 }
 
 }  // namespace sw

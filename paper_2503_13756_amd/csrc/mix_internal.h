@@ -25,7 +25,7 @@ struct MixItem {
     Result *out;        // [count]
     const float2 *d32;  // angle table of n
     const double2 *d64;
-    const int *perm;    // projection work order of (L, n)
+    const PlanLane *perm;  // projection work order of (L, n)
     const int2 *trow;
     int64_t first, count;  // work-index range
     int L, n, Q, levels;

@@ -1,5 +1,5 @@
-// Line projection of two images at once (the hat-weighted line sum of
-// proj_dev.h), for the fused image -> quantile-table kernel.
+// Line projection of one or two images at once (the hat-weighted line sum of
+// proj_dev.h), the routines of every projection and tables kernel.
 //
 // The work split is that of proj_dev.h: a lane owns one (slot angle, bin)
 // item, walks the image rows, and in each row computes the three hat weights
@@ -20,9 +20,9 @@
 // (j2 = j0 + 2, j0 the first column of the hat), so one address serves all
 // twelve products of an image; the second image's strips sit a fixed
 // kImg2Bytes further (an immediate offset of the LDS reads).  The sums are
-// formed in the order of proj_dev.h (w0 term first), and a row's line
-// position depends only on its image row, so the projections are bitwise
-// those of the one-image kernels.
+// formed row by row, w0 term first, and a row's line position depends only on
+// its image row, so the projections are the same bits for any strip height,
+// task split and number of images per block.
 //
 // Staging goes by mirrored pairs: a pixel and its mirror image in the row
 // (F[i][j], F[i][L-1-j]) fill the first half of positions j + 2 and
@@ -225,25 +225,32 @@ __device__ __forceinline__ void s4_store(int nimg, int L, int i0, int rows, cons
 }
 
 // A lane's task here keeps only its row offsets and the LDS address of its
-// slot's constants (c = cos theta, r = tan theta, k1 = 2 - 1/c, k2 = 2 - 3c,
-// the values of make_task), read once per task and strip: the accumulators of
-// two images leave no registers for five constants per task.
+// slot's constants (c = cos theta, r = tan theta, k1 = 2 - 1/c, k2 = 2 - 3c),
+// read once per task and strip: the accumulators of two images leave no
+// registers for five constants per task.
 struct LaneTask2 {
     int ka;           // byte address of the slot's float4 in the table
     float A3, A3n;
     int rlo, rhi;     // wave-uniform
 };
 
-__device__ __forceinline__ LaneTask2 make_task2(const ProjShape &P, const float2 *dtab, int task,
-                                                int lane, int kbase) {
-    const LaneTask t = make_task(P, dtab, task, lane);
-    const int item = task_item(P, task, lane);
+__device__ __forceinline__ LaneTask2 make_task2(const ProjShape &P, int task, int lane,
+                                                int kbase) {
     LaneTask2 u;
-    u.A3 = t.A3;
-    u.A3n = t.A3n;
-    u.rlo = t.rlo;
-    u.rhi = t.rhi;
-    u.ka = kbase + 16 * (item >= 0 ? item / P.L : P.slots);
+    PlanLane pl{-100.f, -100.f, P.slots, -1};  // past the last task: an empty lane
+    u.rlo = 1;
+    u.rhi = 0;
+    if (task < P.ntasks) {
+        pl = P.perm[task * 64 + lane];
+        const int2 rr = P.trow[task];
+        u.rlo = __builtin_amdgcn_readfirstlane(rr.x);
+        u.rhi = __builtin_amdgcn_readfirstlane(rr.y);
+    }
+    u.A3 = pl.A3;
+    u.A3n = pl.A3n;
+    // (pl.slot would save a division, but with it the compiler spills 47
+    // registers of k_tables_mixed)
+    u.ka = kbase + 16 * (pl.item >= 0 ? pl.item / P.L : P.slots);
     return u;
 }
 
@@ -264,8 +271,21 @@ __device__ __forceinline__ void fill_slot_table(const ProjShape &P, const float2
 }
 
 // Accumulate one strip for this wave's tasks and `IMG` images (a missing
-// second image reads its zero strips).  Rows pair from even image rows as in
-// accumulate_strip.
+// second image reads its zero strips).  Task slots are the outer loop (a
+// wave-uniform guard each), rows the inner loop, two per iteration, so that the
+// LDS reads of both rows are in flight together.  Pairs start at even image
+// rows whatever the strip's first row: row 2m sits at 2m r + A3 and row 2m + 1
+// at 2m r + A3n (the row index steps once per pair), so that a row's line
+// position is the same for any strip height.
+//
+// The hat of half-width 1/c (in columns) around u covers at most three
+// columns, j0 = floor(u - 1/c) + 1 .. j0 + 2.  With f = frac(u - 1/c) their
+// weights are
+//   c (1 - f),   1 - c |2 - 1/c - f|,   max(0, 2 - 3c + c f)
+// (c = cos theta in [1/sqrt 2, 1]).  u - 1/c is carried shifted by 3 and
+// clamped to [0.5, L + 2], so that truncation is the floor and j0 stays in
+// [-2, L]: a line clamped there has its whole hat on columns <= 0 or >= L - 1,
+// outside the disk, and so does the clamped position.
 template <int TPW, int IMG, int IB = kImg2Bytes>
 __device__ __forceinline__ void s4_accumulate(const LaneTask2 (&tasks)[TPW], int L,
                                               const float *lds, int i0, int rows,
@@ -350,7 +370,7 @@ __device__ void project_images2(const float *const (&F)[IMG], int nimg, const Pr
     const int kbase = (int)(uintptr_t)(__attribute__((address_space(3))) float4 *)ktab;
     LaneTask2 tasks[TPW];
 #pragma unroll
-    for (int t = 0; t < TPW; ++t) tasks[t] = make_task2(P, dtab, tg0 + wave + t * NW, lane, kbase);
+    for (int t = 0; t < TPW; ++t) tasks[t] = make_task2(P, tg0 + wave + t * NW, lane, kbase);
     // the padding positions (and a missing image's strips) stay zero
     __syncthreads();  // the caller may have used the region and the table
     fill_slot_table<NT>(P, dtab, ktab);
@@ -377,8 +397,7 @@ __device__ void project_images2(const float *const (&F)[IMG], int nimg, const Pr
 // (each group stages the strips again): strips of R <= strip4_rows_max(L) rows in
 // the 64 KiB region at lds, the slot table at ktab; results handed to emit,
 // which must not write to the strips or the table.  bad_out: the image holds
-// a non-finite value (then nothing is emitted).  Bitwise the sums of
-// project_image.
+// a non-finite value (then nothing is emitted).
 template <int NT, int TPW, typename Emit>
 __device__ void project_image4(const float *__restrict__ F, const ProjShape &P,
                                const float2 *__restrict__ dtab, float *lds, float4 *ktab, int R,

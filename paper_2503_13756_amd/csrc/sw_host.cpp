@@ -405,25 +405,33 @@ sw_status get_plan(Ctx *ctx, int L, int n, const sw::ProjPlan **out) {
         *out = &f->second;
         return SW_OK;
     }
-    std::vector<int> perm;
+    std::vector<int> plan, items;
     std::vector<int2> trow;
-    std::vector<int> plan;
     build_plan(L, n, plan, trow);
-    lane_order(L, n, plan, trow, perm);
+    lane_order(L, n, plan, trow, items);
+    std::vector<double> cs, sn;
+    angle_values(n, cs, sn);
+    std::vector<sw::PlanLane> perm(items.size());
+    for (size_t i = 0; i < items.size(); ++i) {
+        const int slot = items[i] >= 0 ? items[i] / L : n / 8 + 1;
+        perm[i] = sw::PlanLane{(float)cs[slot % n], (float)(-sn[slot % n]), slot, items[i]};
+    }
     sw::ProjPlan p;
     p.L = L;
     p.n = n;
     p.ntasks = (int)trow.size();
-    hipError_t e = hipMalloc(&p.perm, sizeof(int) * perm.size());
+    hipError_t e = hipMalloc(&p.perm, sizeof(sw::PlanLane) * perm.size());
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(projection plan)");
     e = hipMalloc(&p.trow, sizeof(int2) * trow.size());
     if (e != hipSuccess) {
         (void)hipFree(p.perm);
         return hip_fail(e, "hipMalloc(projection plan)");
     }
-    e = hipMemcpy(p.perm, perm.data(), sizeof(int) * perm.size(), hipMemcpyHostToDevice);
+    e = hipMemcpy(p.perm, perm.data(), sizeof(sw::PlanLane) * perm.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(p.trow, trow.data(), sizeof(int2) * trow.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = sw::launch_plan_lanes(p.perm, (int)perm.size(), L, nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
         (void)hipFree(p.perm);
         (void)hipFree(p.trow);

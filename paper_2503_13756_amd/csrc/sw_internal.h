@@ -12,21 +12,9 @@ constexpr int kMaxN = 512;
 constexpr int kMaxQ = 512;
 constexpr int kMaxTopK = 8;
 
-// LDS image strips of the projection.  A strip holds R image rows and the
-// same R image columns transposed (two "kinds", kKindFloats apart).  A strip
-// row is stored as sliding windows: the 16-byte chunk q (floats 4q .. 4q+3
-// of the row) holds elements q - kStripPad .. q - kStripPad + 3 of the row
-// (zero outside the image), so that the window of four consecutive elements
-// starting at element e is the one aligned chunk e + kStripPad, and lanes
-// reading neighbouring windows read neighbouring chunks.  Rows hold an odd
-// number of chunks, so that consecutive rows start in different banks.
-constexpr int kStripPad = 3;
-constexpr int kKindFloats = 8192;
-constexpr int kStripFloats = 2 * kKindFloats;  // 64 KiB
-// chunks per strip row: windows start at elements -3 .. L
-__host__ __device__ inline int strip_stride(int L) { return (L + kStripPad + 1) | 1; }
-__host__ __device__ inline int strip_row_floats(int L) { return 4 * strip_stride(L); }
-__host__ __device__ inline int strip_rows_max(int L) { return kKindFloats / strip_row_floats(L); }
+// LDS region of the projection's image strips (proj2_dev.h) in a 512-thread
+// block, two of which share a compute unit: 64 KiB.
+constexpr int kStripFloats = 16384;
 // Rows of the four-kind strips of one image (the persistent mixed tables
 // kernel): (L + 5) | 1 positions of 16 bytes per row in the 64 KiB region,
 // staged in at most four passes of 512 threads both over the strip's rows of
@@ -53,9 +41,19 @@ __host__ __device__ inline int strip4_rows_max(int L) {
 __host__ __device__ inline int proj_ntasks(int L, int n) {
     return ((n / 8 + 1) * ((L + 7) / 8) + 7) / 8;
 }
+// One lane of a task: its item, the item's slot angle (slots for none) and
+// the line's offsets: the line of bin b crosses image row i (c0 = (L-1)/2,
+// c = cos theta, r = tan theta) at column u(i) = (b - c0)/c + c0 + r (i - c0),
+// and A3 = u(0) - 1/c + 3, A3n = A3 + r, each rounded once from FP64
+// (launch_plan_lanes; every projection kernel reads these, so that all form
+// the same positions).
+struct PlanLane {
+    float A3, A3n;
+    int slot, item;
+};
 struct ProjPlan {
     int L = 0, n = 0, ntasks = 0;
-    int *perm = nullptr;   // [ntasks * 64]
+    PlanLane *perm = nullptr;  // [ntasks * 64]
     int2 *trow = nullptr;  // [ntasks]
 };
 
@@ -80,6 +78,10 @@ struct Result {
     int32_t status;
 };
 static_assert(sizeof(Result) == 24, "sw_result is 24 bytes");
+
+// Fills A3 and A3n of the lanes [0, count) of a plan, which hold (cos theta,
+// -sin theta) of their slots (in FP32, from the angle table) on entry.
+hipError_t launch_plan_lanes(PlanLane *lanes, int count, int L, hipStream_t s);
 
 // ---- launchers (each returns hipGetLastError() after its launches) ----
 // split: one block per (image, task group), for batches too small to fill the

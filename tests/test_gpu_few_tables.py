@@ -49,9 +49,12 @@ def test_reference_spectra_row_split(api, L, n, Q, refs):
 
 # images per launch: one, several, one below and at the default small-batch
 # limit of a 256-unit device; sides with one strip, with several, at the edges
-# of the staging; columns by half waves (L <= 128) and by whole waves
+# of the staging; columns by half waves (L <= 128) and by whole waves; (150,
+# 192, 108) and (255, 512, 8): two images per 1024-thread block, fused and in
+# several task groups
 @pytest.mark.parametrize("L,n,Q", [(8, 8, 8), (39, 48, 48), (97, 24, 20), (128, 128, 128),
-                                   (129, 96, 60), (256, 72, 256)])
+                                   (129, 96, 60), (256, 72, 256), (150, 192, 108),
+                                   (255, 512, 8)])
 @pytest.mark.parametrize("N", [1, 5, 255])
 def test_small_batches_equal_large_ones(api, tmp_path, L, n, Q, N):
     """The launches of a small batch (several blocks per image) against those of
