@@ -168,7 +168,8 @@ struct Len {
 template <int NT, bool POW2>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_fourier(const float *__restrict__ img, int64_t N,
                                                 FourierShape S, FourierTabs T,
-                                                float2 *__restrict__ scratch, float *__restrict__ pmf) {
+                                                float2 *__restrict__ scratch, float *__restrict__ pmf,
+                                                unsigned *clear) {
     extern __shared__ __align__(16) float2 lds2[];
     __shared__ int sbad;
     const int L = S.L, M = L >> 1, n = S.n, Nf = S.Nf, H = S.H, lgNf = S.lgNf, lgL = S.lgL;
@@ -204,7 +205,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void
     for (int64_t g = blockIdx.x; g < N; g += gridDim.x) {
         const float *F = img + g * (int64_t)L * L;
         __syncthreads();  // previous image done with sbad and the buffers
-        if (threadIdx.x == 0) sbad = 0;
+        if (threadIdx.x == 0) {
+            sbad = 0;
+            if (clear) clear[g] = 0u;
+        }
         int bad = 0;
         // 1. rows, two per transform
         for (int p0 = 0; p0 < M; p0 += GR) {
@@ -371,7 +375,7 @@ int fourier_blocks_per_cu(int L, int Nf) {
 }
 
 hipError_t launch_fourier(const float *img, int64_t N, const FourierShape &S, const FourierTabs &T,
-                          void *scratch, int slots, float *pmf, hipStream_t s) {
+                          void *scratch, int slots, float *pmf, hipStream_t s, unsigned *clear) {
     if (N <= 0) return hipSuccess;
     constexpr int NT = kFourierNT;
     const size_t lds = fourier_lds_bytes(S.L, S.Nf);
@@ -379,10 +383,10 @@ hipError_t launch_fourier(const float *img, int64_t N, const FourierShape &S, co
     const int grid = (int)(N < slots ? N : slots);
     if (is_pow2(S.L))
         hipLaunchKernelGGL((k_fourier<NT, true>), dim3(grid), dim3(NT), lds, s, img, N, S, T,
-                           (float2 *)scratch, pmf);
+                           (float2 *)scratch, pmf, clear);
     else
         hipLaunchKernelGGL((k_fourier<NT, false>), dim3(grid), dim3(NT), lds, s, img, N, S, T,
-                           (float2 *)scratch, pmf);
+                           (float2 *)scratch, pmf, clear);
     return hipGetLastError();
 }
 

@@ -122,7 +122,7 @@ template <int NT, int KP>
 __global__ __launch_bounds__(NT) void k_project_few(const float *__restrict__ img, int64_t N,
                                                     ProjShape P, const float2 *__restrict__ dtab,
                                                     float *__restrict__ pmf, int R,
-                                                    int strip_floats) {
+                                                    int strip_floats, unsigned *clear) {
     constexpr int NW = NT / 64;
     extern __shared__ __align__(16) float lds[];
     const int64_t g = blockIdx.x;
@@ -131,6 +131,7 @@ __global__ __launch_bounds__(NT) void k_project_few(const float *__restrict__ im
     const float *const F[1] = {img + g * (int64_t)L * L};
     float *out = pmf + g * (int64_t)n * L;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (clear && blockIdx.y == 0 && threadIdx.x == 0) clear[g] = 0u;
     float acc[1][1][4];
     int bad[1];
     project_images2<NT, 1, 1, KP>(F, 1, P, dtab, lds, (float4 *)(lds + strip_floats), R, tg0, acc,
@@ -221,7 +222,8 @@ static hipError_t launch_project2_t(const float *img, int64_t N, const ProjShape
 // cover the strip's rows.
 template <int NT, int KP>
 static hipError_t launch_project_few_t(const float *img, int64_t N, const ProjShape &P, int R,
-                                       const float2 *dtab, float *pmf, hipStream_t s) {
+                                       const float2 *dtab, float *pmf, unsigned *clear,
+                                       hipStream_t s) {
     static const hipError_t attr = hipFuncSetAttribute(
         (const void *)k_project_few<NT, KP>, hipFuncAttributeMaxDynamicSharedMemorySize,
         152 * 1024);
@@ -230,12 +232,13 @@ static hipError_t launch_project_few_t(const float *img, int64_t N, const ProjSh
     const size_t lds = sizeof(float) * strip_floats + sizeof(float4) * (P.slots + 1);
     const int groups = (P.ntasks + NT / 64 - 1) / (NT / 64);
     hipLaunchKernelGGL((k_project_few<NT, KP>), dim3((unsigned)N, (unsigned)groups), dim3(NT), lds,
-                       s, img, N, P, dtab, pmf, R, strip_floats);
+                       s, img, N, P, dtab, pmf, R, strip_floats, clear);
     return hipGetLastError();
 }
 
 static hipError_t launch_project_few(const float *img, int64_t N, const ProjShape &P,
-                                     const float2 *dtab, float *pmf, hipStream_t s) {
+                                     const float2 *dtab, float *pmf, unsigned *clear,
+                                     hipStream_t s) {
     constexpr int NT = 512;
     static const int cus = [] {
         int dev = 0, c = 0;
@@ -248,10 +251,10 @@ static hipError_t launch_project_few(const float *img, int64_t N, const ProjShap
     const int most = s4_rows<NT, 8>(P.L, bytes), strips = (P.L + most - 1) / most;
     const int R = (P.L + strips - 1) / strips;  // <= most: strips of nearly equal height
     if (s4_rows<NT, 2>(P.L, bytes) >= R)
-        return launch_project_few_t<NT, 2>(img, N, P, R, dtab, pmf, s);
+        return launch_project_few_t<NT, 2>(img, N, P, R, dtab, pmf, clear, s);
     if (s4_rows<NT, 4>(P.L, bytes) >= R)
-        return launch_project_few_t<NT, 4>(img, N, P, R, dtab, pmf, s);
-    return launch_project_few_t<NT, 8>(img, N, P, R, dtab, pmf, s);
+        return launch_project_few_t<NT, 4>(img, N, P, R, dtab, pmf, clear, s);
+    return launch_project_few_t<NT, 8>(img, N, P, R, dtab, pmf, clear, s);
 }
 
 template <int NT, int TPW>
@@ -268,13 +271,14 @@ static hipError_t launch_project2_large(const float *img, int64_t N, const ProjS
 }
 
 hipError_t launch_project(const float *img, int64_t N, Geo g, const AngleTable &t,
-                          const ProjPlan &pp, float *pmf, hipStream_t s, bool split) {
+                          const ProjPlan &pp, float *pmf, hipStream_t s, bool split,
+                          unsigned *clear) {
     if (N <= 0) return hipSuccess;
     ProjShape P = proj_shape(g.L, g.n);  // 64 KiB of strips: two blocks per CU
     if (pp.L != g.L || pp.n != g.n || pp.ntasks != P.ntasks) return hipErrorInvalidValue;
     P.perm = pp.perm;
     P.trow = pp.trow;
-    if (split) return launch_project_few(img, N, P, t.d32, pmf, s);
+    if (split) return launch_project_few(img, N, P, t.d32, pmf, clear, s);
     const int w512 = tasks_per_wave(P.ntasks, 512);
     if (s4_supported(g.L)) {  // two images per block where all tasks fit one group of six
         const int64_t table = (int64_t)g.n * g.L;  // room to park the second image's sums

@@ -90,23 +90,31 @@ __global__ __launch_bounds__(NT) void k_quantile_rf(const float *__restrict__ pf
 // one per image, so that all columns are inverted at once: a column is a chain
 // of FP64 scans and interpolations of about 4 us, and one block of 16 waves
 // went through the columns of one image in turn.  The column sums (and the
-// masses the image's aux needs) go to scratch, where k_quantile_aux reduces
-// them in the order of quantile_phase: the same bits.  One image, both
-// kernels: 7.8 -> 5.3 us at L = n = Q = 64, 22 -> 9 at 128, 82 -> 10 at 256,
-// the two signed parts at 128 55 -> 12.
+// masses the image's aux needs) go to scratch, and the image's last block to
+// finish reduces them in the order of quantile_phase: the same bits whichever
+// block that is.  One image: 7.8 -> 5.7 us at L = n = Q = 64, 22 -> 7.6 at
+// 128, 82 -> 9.0 at 256, the two signed parts at 128 55 -> 12.
+//
+// done[g] counts the finished blocks of image g; 0 before the launch (the
+// projectors clear it).  Every block publishes its sums with a device-scope
+// release before it counts; the one that counts last acquires.
 constexpr int kColsPerBlock = 8;
 
 template <int NT, bool RF>
 __global__ __launch_bounds__(NT) void k_quantile_cols(const float *__restrict__ pmf, int L, int n,
-                                                      int Q, int levels, float *__restrict__ qt,
-                                                      double *__restrict__ colS,
-                                                      double *__restrict__ colM) {
+                                                      int Q, int levels,
+                                                      const double2 *__restrict__ d64,
+                                                      float *__restrict__ qt,
+                                                      double *__restrict__ aux, double *colS,
+                                                      double *colM, unsigned *done) {
     constexpr int NW = NT / 64, TC = kColsPerBlock;
     extern __shared__ __align__(16) float Ut[];  // [Q][TC + 1]
     __shared__ double cs[2 * TC];
+    __shared__ int last;
     const int64_t g = blockIdx.x;
     const int k0 = TC * (int)blockIdx.y, part = RF ? (int)blockIdx.z : 0;
     constexpr int parts = RF ? 2 : 1;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float sign = part ? -1.f : 1.f;
     const float *P = pmf + g * (int64_t)n * L;
     auto col = [&](int k, int b) {
@@ -118,18 +126,12 @@ __global__ __launch_bounds__(NT) void k_quantile_cols(const float *__restrict__ 
     if (L <= 128) invert_tile<NT, true>(col, L, Q, levels, TC, k0, Ut, cs - 2 * k0, &mass0);
     else invert_tile<NT, false>(col, L, Q, levels, TC, k0, Ut, cs - 2 * k0, &mass0);
     __syncthreads();
-    float *U = qt + (g * parts + part) * (int64_t)Q * n + k0;
-    for (int idx = threadIdx.x; idx < Q * TC; idx += NT) {
-        const int j = idx / TC, kl = idx - j * TC;
-        U[(int64_t)j * n + kl] = Ut[j * (TC + 1) + kl];
-    }
     if (threadIdx.x < 2 * TC)
         colS[((g * parts + part) * n + k0) * 2 + threadIdx.x] = cs[threadIdx.x];
     if (!RF) {
         if (k0 == 0 && threadIdx.x == 0) colM[g * n] = mass0;  // column 0 is inverted by wave 0
     } else if (part == 0) {
         // the smaller part mass of each column, NaN for a NaN value
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         for (int kl = wave; kl < TC; kl += NW) {
             double sp = 0.0, sm = 0.0;
             int bad = 0;
@@ -147,28 +149,30 @@ __global__ __launch_bounds__(NT) void k_quantile_cols(const float *__restrict__ 
                     bad ? __longlong_as_double(0x7ff8000000000000LL) : fmin(sp, sm);
         }
     }
-}
-
-// aux of each image from the column sums: one wave per image.
-template <bool RF>
-__global__ __launch_bounds__(64) void k_quantile_aux(const double *__restrict__ colS,
-                                                     const double *__restrict__ colM, int n, int Q,
-                                                     const double2 *__restrict__ d64,
-                                                     double *__restrict__ aux) {
-    constexpr int parts = RF ? 2 : 1;
-    const int64_t g = blockIdx.x;
-    const int lane = threadIdx.x;
-    double part[parts][3];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();  // the block's sums, before the count
+        last = atomicAdd(done + g, 1u) == gridDim.y * parts - 1;
+    }
+    float *U = qt + (g * parts + part) * (int64_t)Q * n + k0;
+    for (int idx = threadIdx.x; idx < Q * TC; idx += NT) {
+        const int j = idx / TC, kl = idx - j * TC;
+        U[(int64_t)j * n + kl] = Ut[j * (TC + 1) + kl];
+    }
+    __syncthreads();
+    if (!last || wave != 0 || !aux) return;
+    __threadfence();  // every block's sums are visible from here on
+    double sums[parts][3];
 #pragma unroll
     for (int h = 0; h < parts; ++h)
-        column_aux(colS + (g * parts + h) * 2 * n, n, Q, d64, lane, part[h]);
+        column_aux(colS + (g * parts + h) * 2 * n, n, Q, d64, lane, sums[h]);
     double *A = aux + 4 * g;
     if (!RF) {
         if (lane == 0) {
             A[0] = colM[g * n];
-            A[1] = part[0][0];
-            A[2] = part[0][1];
-            A[3] = part[0][2];
+            A[1] = sums[0][0];
+            A[2] = sums[0][1];
+            A[3] = sums[0][2];
         }
         return;
     }
@@ -184,32 +188,33 @@ __global__ __launch_bounds__(64) void k_quantile_aux(const double *__restrict__ 
     bad = __any(bad);
     if (lane == 0) {
         A[0] = bad ? __longlong_as_double(0x7ff8000000000000LL) : mn;
-        A[1] = part[0][0] + part[parts - 1][0];
-        A[2] = 0.5 * (part[0][1] + part[parts - 1][1]);
-        A[3] = 0.5 * (part[0][2] + part[parts - 1][2]);
+        A[1] = sums[0][0] + sums[parts - 1][0];
+        A[2] = 0.5 * (sums[0][1] + sums[parts - 1][1]);
+        A[3] = 0.5 * (sums[0][2] + sums[parts - 1][2]);
     }
 }
 
 size_t quantile_cols_bytes(int64_t N, int n, int parts) {
-    return sizeof(double) * (size_t)N * n * (2 * parts + 1);
+    return sizeof(double) * (size_t)N * (n * (2 * parts + 1) + 1);
 }
+
+unsigned *quantile_cols_done(void *cols) { return (unsigned *)cols; }
 
 template <bool RF>
 static hipError_t launch_quantile_cols(const float *pmf, int64_t N, Geo g, const AngleTable &t,
                                        float *qt, double *aux, double *cols, hipStream_t s) {
     constexpr int parts = RF ? 2 : 1;
-    double *colM = cols + (size_t)N * g.n * 2 * parts;
+    // a double's room for each image's counter, then the sums, then the masses
+    unsigned *done = quantile_cols_done(cols);
+    double *colS = cols + N, *colM = colS + (size_t)N * g.n * 2 * parts;
     const dim3 grid((unsigned)N, (unsigned)(g.n / kColsPerBlock), parts);  // n: a multiple of 8
     const size_t lds = sizeof(float) * g.Q * (kColsPerBlock + 1);
     if (g.L <= 128)  // two columns per wave: four waves take a block's eight at once
         hipLaunchKernelGGL((k_quantile_cols<256, RF>), grid, dim3(256), lds, s, pmf, g.L, g.n, g.Q,
-                           g.levels, qt, cols, colM);
+                           g.levels, t.d64, qt, aux, colS, colM, done);
     else
         hipLaunchKernelGGL((k_quantile_cols<512, RF>), grid, dim3(512), lds, s, pmf, g.L, g.n, g.Q,
-                           g.levels, qt, cols, colM);
-    if (aux)
-        hipLaunchKernelGGL(k_quantile_aux<RF>, dim3((unsigned)N), dim3(64), 0, s, cols, colM, g.n,
-                           g.Q, t.d64, aux);
+                           g.levels, t.d64, qt, aux, colS, colM, done);
     return hipGetLastError();
 }
 

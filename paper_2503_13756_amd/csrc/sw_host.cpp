@@ -1049,7 +1049,8 @@ sw_status sw_tables(void *ctx, const float *img, int64_t N, const sw_geom *g, fl
     for (int64_t i0 = 0; i0 < N; i0 += chunk) {
         const int64_t m = N - i0 < chunk ? N - i0 : chunk;
         hipError_t e = sw::launch_project(img + i0 * (int64_t)geo.L * geo.L, m, geo, *t, *pp,
-                                          (float *)pmf, s, small);
+                                          (float *)pmf, s, small,
+                                          small ? sw::quantile_cols_done(cols) : nullptr);
         if (e != hipSuccess) return hip_fail(e, "k_project launch");
         e = sw::launch_quantiles((const float *)pmf, m, geo, *t, qt + i0 * (int64_t)geo.Q * geo.n,
                                  aux ? aux + 4 * i0 : nullptr, s, small, cols);
@@ -1137,7 +1138,8 @@ sw_status sw_tables_rf(void *ctx, const float *img, int64_t N, const sw_geom *g,
     for (int64_t i0 = 0; i0 < N; i0 += chunk) {
         const int64_t m = N - i0 < chunk ? N - i0 : chunk;
         hipError_t e = sw::launch_project(img + i0 * (int64_t)geo.L * geo.L, m, geo, *t, *pp,
-                                          (float *)pmf, s, small);
+                                          (float *)pmf, s, small,
+                                          small ? sw::quantile_cols_done(cols) : nullptr);
         if (e != hipSuccess) return hip_fail(e, "k_project launch");
         e = sw::launch_ramp((const float *)pmf, (float *)pmf, m * (int64_t)geo.n, geo.L, hx, s);
         if (e != hipSuccess) return hip_fail(e, "k_ramp launch");
@@ -1263,7 +1265,8 @@ static sw_status tables_fourier(void *ctx, const float *img, int64_t N, const sw
     for (int64_t i0 = 0; i0 < N; i0 += chunk) {
         const int64_t m = N - i0 < chunk ? N - i0 : chunk;
         hipError_t e = sw::launch_fourier(img + i0 * (int64_t)geo.L * geo.L, m, S, T, slot_mem,
-                                          slots, pmf, s);
+                                          slots, pmf, s,
+                                          c->small(m) ? sw::quantile_cols_done(cols) : nullptr);
         if (e != hipSuccess) return hip_fail(e, "k_fourier launch");
         e = sw::launch_quantiles(pmf, m, geo, *dirs, qt + i0 * (int64_t)geo.Q * geo.n,
                                  aux ? aux + 4 * i0 : nullptr, s, c->small(m), cols);

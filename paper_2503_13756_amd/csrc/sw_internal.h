@@ -85,13 +85,16 @@ hipError_t launch_plan_lanes(PlanLane *lanes, int count, int L, hipStream_t s);
 
 // ---- launchers (each returns hipGetLastError() after its launches) ----
 // split: one block per (image, task group), for batches too small to fill the
-// device with one block per image
+// device with one block per image; clear (with split; nullable): [N], set to 0
 hipError_t launch_project(const float *img, int64_t N, Geo g, const AngleTable &t,
-                          const ProjPlan &pp, float *pmf, hipStream_t s, bool split = false);
+                          const ProjPlan &pp, float *pmf, hipStream_t s, bool split = false,
+                          unsigned *clear = nullptr);
 // small: for batches too small to fill the device with one block per image;
 // cols: scratch of quantile_cols_bytes() (one part, or two for the signed
-// parts) for the launches that take many blocks per image, or null
+// parts) for the launches that take many blocks per image, or null.  Its
+// quantile_cols_done(), N counters, must be 0: the projectors clear them.
 size_t quantile_cols_bytes(int64_t N, int n, int parts);
+unsigned *quantile_cols_done(void *cols);
 hipError_t launch_quantiles(const float *pmf, int64_t N, Geo g, const AngleTable &t, float *qt,
                             double *aux, hipStream_t s, bool small = false,
                             double *cols = nullptr);
