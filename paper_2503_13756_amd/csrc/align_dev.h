@@ -40,11 +40,13 @@ __device__ __forceinline__ float2 bf16r2(float2 v) {
 // Load complex rows p0 .. p0+rows-1 of a [Q][n] real table: row p packs table
 // rows 2p (real part) and 2p+1 (imaginary part).
 template <int NT>
-__device__ void load_packed(float2 *Z, const float *__restrict__ T, int n, int p0, int rows) {
+__device__ __forceinline__ void load_packed(float2 *Z, const float *__restrict__ T, int n, int p0,
+                                            int rows) {
+    const float inv = __builtin_amdgcn_rcpf((float)n);
+    const float *T0 = T + (int64_t)(2 * p0) * n;
     for (int idx = threadIdx.x; idx < rows * n; idx += NT) {
-        const int pl = idx / n, k = idx - pl * n;
-        const int j = 2 * (p0 + pl);
-        Z[idx] = make_float2(T[(int64_t)j * n + k], T[(int64_t)(j + 1) * n + k]);
+        const float *t = T0 + idx + __mul24(div_small(idx, inv), n);
+        Z[idx] = make_float2(t[0], t[n]);
     }
 }
 
@@ -72,51 +74,6 @@ __device__ __forceinline__ void argmin_merge(double &v, int &i, double v2, int i
     }
 }
 
-template <int NT>
-__device__ int block_argmin(const double *D, int n, double *rv, int *ri) {
-    double v = __builtin_inf();
-    int i = 0x7fffffff;
-    for (int l = threadIdx.x; l < n; l += NT) argmin_merge(v, i, D[l], l);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const double v2 = __shfl_xor(v, off, 64);
-        const int i2 = __shfl_xor(i, off, 64);
-        argmin_merge(v, i, v2, i2);
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) {
-        rv[wave] = v;
-        ri[wave] = i;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < NT / 64; ++w) argmin_merge(v, i, rv[w], ri[w]);
-        ri[0] = i;
-    }
-    __syncthreads();
-    const int r = ri[0];
-    __syncthreads();
-    return r;
-}
-
-template <int NT>
-__device__ float block_sum(float v, float *red) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    float s = 0.f;
-    if (threadIdx.x == 0) {
-        for (int w = 0; w < NT / 64; ++w) s += red[w];
-        red[0] = s;
-    }
-    __syncthreads();
-    s = red[0];
-    __syncthreads();
-    return s;
-}
-
 // b(l) = a_U - e^{i theta_l} a_V
 __device__ __forceinline__ double2 trans_moment(const double *au, const double *av, double2 d) {
     const double c = d.x, s = -d.y;
@@ -125,9 +82,10 @@ __device__ __forceinline__ double2 trans_moment(const double *au, const double *
 
 // Angle spectra of the packed rows [pbeg, pend) of one [Q][n] table, at most
 // CH of them at a time: emit(p, w, xe, xo) gets the spectra of table rows 2p
-// and 2p + 1 at every w in [0, n/2].  Each packed row is transformed on its
-// own, so its spectra do not depend on the split.  lds: n + 2 CH n float2.
-template <int NT, typename Emit>
+// and 2p + 1 at every w in [0, n/2], neighbouring threads neighbouring w (or,
+// with ROWS, neighbouring p).  Each packed row is transformed on its own, so
+// its spectra do not depend on the split.  lds: n + 2 CH n float2.
+template <int NT, bool ROWS, typename Emit>
 __device__ void spectrum_rows(const float *__restrict__ T, int n, int pbeg, int pend, int CH,
                               const float2 *__restrict__ tw32, float2 *lds2, Emit emit) {
     const int Wn = n / 2 + 1;
@@ -142,8 +100,11 @@ __device__ void spectrum_rows(const float *__restrict__ T, int n, int pbeg, int 
         load_packed<NT>(Z0, T, n, p0, rows);
         __syncthreads();
         const float2 *Z = fft_rows<NT>(Z0, Z1, rows, n, tw);
+        const int len = ROWS ? rows : Wn;
+        const float inv = __builtin_amdgcn_rcpf((float)len);
         for (int idx = threadIdx.x; idx < rows * Wn; idx += NT) {
-            const int w = idx / rows, pl = idx - w * rows;
+            const int q = div_small(idx, inv), o = idx - __mul24(q, len);
+            const int w = ROWS ? q : o, pl = ROWS ? o : q;
             float2 xe, xo;
             unpack(Z, pl, n, w, xe, xo);
             emit(p0 + pl, w, xe, xo);
@@ -152,10 +113,12 @@ __device__ void spectrum_rows(const float *__restrict__ T, int n, int pbeg, int 
     __syncthreads();
 }
 
-// The spectra of rows 2p and 2p + 1 at w into spec[w][j] (float2).
-__device__ __forceinline__ void store_spectrum(float2 *spec, int Q, int p, int w, float2 xe,
+// FP32 spectra of a table as the alignment reads them: spec[p][w], w <= n/2,
+// the spectra of rows 2p and 2p + 1 side by side (a float4), so that
+// neighbouring frequencies are neighbours in memory.
+__device__ __forceinline__ void store_spectrum(float4 *spec, int Wn, int p, int w, float2 xe,
                                                float2 xo) {
-    *(float4 *)(spec + (int64_t)w * Q + 2 * p) = make_float4(xe.x, xe.y, xo.x, xo.y);
+    spec[(int64_t)p * Wn + w] = make_float4(xe.x, xe.y, xo.x, xo.y);
 }
 
 // The register-FFT alignment's coefficients (align128_dev.h) of packed row p
@@ -176,85 +139,142 @@ __device__ __forceinline__ void store_gamma128(float2 *gam, float2 *gx, int p, i
     else gx[2 * p] = beta;
 }
 
-// Alignment of one table pair by one block: spectra of V, spectral dot with
-// the reference spectrum Uh, inverse transform over the lags, translation
-// correction, top-k, FP32 rescore; writes *res (and curve[0..n) if given).
-// lds: n + 2 kFftElems + Wn G float2 followed by n doubles.
-struct PairJob {
-    const float *U, *V;       // [Q][n] tables
-    const double *au, *av;    // aux of both
-    const float2 *Uh;         // [Wn][Q] FP32 spectrum of U
-    Result *res;
-    float *curve;             // nullable, [n]
-    int status;               // precomputed status (0 = compute)
+// Alignment of one image table V with `nr` <= RG reference tables by one
+// block: spectra of V (once for all references), spectral dots with the
+// references' spectra, inverse transform over the lags, translation
+// correction, top-k, FP32 rescore; writes the result of every pair (and its
+// curve).  A pair's arithmetic does not depend on RG or nr.
+//
+// What bounds it is the issue of vector instructions: index arithmetic (no
+// integer divisions here), the transforms and the rescore.  Sharing the image's
+// transforms between references takes the transforms, two thirds of a pair's
+// work at n = 64, out of all but one of them.  16 x 2,000 pairs at L = n = Q = 64
+// 517 -> 199 us; one reference against 1,500 images at 256 508 -> 452 us, against
+// 1,031 at L = 39 22 -> 19 us.
+struct PairsJob {
+    const float *U, *V;    // [nr][Q][n] and [Q][n] tables
+    const double *au, *av; // aux of both, [nr][4] and [4]
+    const float4 *Uh;      // [nr][Q/2][Wn] FP32 spectra of U (store_spectrum)
+    Result *res;           // the pair of reference r: res[r stride], curve + r stride n
+    float *curve;          // nullable
+    int64_t stride;
+    int nr;
+    int status;            // 3: bad pair index (nr is 1; nothing is read)
 };
 
-template <int NT>
-__device__ void align_pair_block(const PairJob &job, Geo g, int mode, int bf16, int top_k,
-                                 const float2 *__restrict__ tw32, const double2 *__restrict__ tw64,
-                                 float2 *lds2) {
-    __shared__ double rv[NT / 64];
-    __shared__ int ri[NT / 64];
-    __shared__ float rf[NT / 64];
-    __shared__ int cand[kMaxTopK];
-    const int n = g.n, Q = g.Q, Wn = n / 2 + 1;
-    const int G = Wn >= NT ? 1 : NT / Wn;
+constexpr int kAlignSlots = 8;  // candidates rescored at a time (>= kMaxTopK)
+
+// LDS of align_pairs_block in bytes: the angle table, the two FFT buffers,
+// the spectral sums and D* of every reference.
+__host__ __device__ inline size_t align_pairs_lds(int n, int RG) {
+    return sizeof(float2) * (size_t)(n + 2 * kFftElems + RG * (n / 2 + 2)) +
+           sizeof(double) * (size_t)(RG * n);
+}
+
+template <int NT, int RG>
+__device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16, int top_k,
+                                  const float2 *__restrict__ tw32,
+                                  const double2 *__restrict__ tw64, float2 *lds2) {
+    constexpr int NW = NT / 64;
+    constexpr int IT = RG == 1 ? 2 : 1;  // spectral sums per thread (n = 512: 257 of them)
+    __shared__ int lagS[RG * kMaxTopK];
+    __shared__ float2 shiftS[RG * kMaxTopK];
+    __shared__ float valS[RG * kMaxTopK];
+    __shared__ float red[NW][kAlignSlots];
+    const int n = g.n, Q = g.Q, Wn = n / 2 + 1, half = n / 2, K = top_k;
+    // an opaque copy of the thread index: in a persistent caller, what is
+    // derived from it is formed per job instead of being kept live across jobs
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nr = RG == 1 ? 1 : job.nr;
     float2 *tw = lds2;
     float2 *Z0 = tw + n;
     float2 *Z1 = Z0 + kFftElems;
-    float2 *Sacc = Z1 + kFftElems;
-    double *D = (double *)(Sacc + Wn * G);
-    Result *res = job.res;
-    __syncthreads();  // the previous job of this block may still read LDS
-    if (job.status) {
-        if (threadIdx.x == 0) {
+    float2 *S = Z1 + kFftElems;                      // [RG][Wn + 1]
+    double *D = (double *)(S + RG * (n / 2 + 2));    // [RG][n]
+    auto fail = [&](int r, int status) {
+        Result *res = job.res + r * job.stride;
+        if (tid == 0) {
             res->rot_index = 0;
             res->theta_rad = 0.f;
             res->shift_px[0] = res->shift_px[1] = 0.f;
             res->sw2sq = __int_as_float(0x7fc00000);
-            res->status = job.status;
+            res->status = status;
         }
         if (job.curve)
-            for (int l = threadIdx.x; l < n; l += NT) job.curve[l] = __int_as_float(0x7fc00000);
+            for (int l = tid; l < n; l += NT)
+                job.curve[r * job.stride * n + l] = __int_as_float(0x7fc00000);
+    };
+    __syncthreads();  // the previous job of this block may still read LDS
+    if (job.status) {
+        fail(0, job.status);
         return;
     }
-    const float *U = job.U, *V = job.V;
-    const double *au = job.au, *av = job.av;
-    const float2 *Uh = job.Uh;
+    const double *av = job.av;
+    auto status_of = [&](int r) {  // uniform
+        const double *au = job.au + 4 * r;
+        if (isnan(au[0]) || isnan(av[0])) return 2;
+        return !(au[0] > 0.0) || !(av[0] > 0.0) ? 1 : 0;
+    };
+    int live = 0;  // references whose pair is computed
+    for (int r = 0; r < nr; ++r) {
+        const int st = status_of(r);
+        if (st) fail(r, st);
+        else live |= 1 << r;
+    }
+    if (!live) return;
 
-    for (int i = threadIdx.x; i < n; i += NT) tw[i] = tw32[i];
-    for (int i = threadIdx.x; i < Wn * G; i += NT) Sacc[i] = make_float2(0.f, 0.f);
+    for (int i = tid; i < n; i += NT) tw[i] = tw32[i];
 
-    // --- spectra of V and the spectral dot with conj(U^)
+    // --- spectra of V and the spectral dots with conj(U^).  Thread (gg, w),
+    // w fastest, sums the packed rows gg, gg + G, .. of every chunk.
+    const int G = Wn >= NT ? 1 : NT / Wn, items = Wn * G;
+    float2 s[IT][RG];
+#pragma unroll
+    for (int i = 0; i < IT; ++i)
+#pragma unroll
+        for (int r = 0; r < RG; ++r) s[i][r] = make_float2(0.f, 0.f);
+    const int gg0 = div_small(tid, __builtin_amdgcn_rcpf((float)Wn));
     const int CH = fft_chunk_rows(n, Q);
+    const int64_t specs = (int64_t)(Q / 2) * Wn;  // of one reference
     for (int p0 = 0; p0 < Q / 2; p0 += CH) {
         const int rows = min(CH, Q / 2 - p0);
         __syncthreads();
-        load_packed<NT>(Z0, V, n, p0, rows);
+        load_packed<NT>(Z0, job.V, n, p0, rows);
         __syncthreads();
         const float2 *Z = fft_rows<NT>(Z0, Z1, rows, n, tw);
         // the rounding to bf16 as a compile-time choice: as a run-time flag
         // the compiler rounds on both paths and selects
         auto dot = [&](auto round) {
-            for (int it = threadIdx.x; it < Wn * G; it += NT) {
-                const int w = it / G, gg = it - w * G;
-                float2 s = Sacc[it];
+#pragma unroll
+            for (int i = 0; i < IT; ++i) {
+                const int it = tid + i * NT;
+                if (i > 0 && items <= NT) break;  // uniform
+                const int gg = i ? 0 : gg0, w = i ? it : it - __mul24(gg0, Wn);
+                if (it >= items) continue;
                 for (int pl = gg; pl < rows; pl += G) {
                     float2 xe, xo;
                     unpack(Z, pl, n, w, xe, xo);
-                    const float4 uu = *(const float4 *)(Uh + (int64_t)w * Q + 2 * (p0 + pl));
-                    float2 ue = make_float2(uu.x, uu.y), uo = make_float2(uu.z, uu.w);
+                    const float4 *uh = job.Uh + (int64_t)(p0 + pl) * Wn + w;
                     if constexpr (decltype(round)::value) {
                         xe = bf16r2(xe);
                         xo = bf16r2(xo);
-                        ue = bf16r2(ue);
-                        uo = bf16r2(uo);
                     }
-                    // conj(ue) * xe + conj(uo) * xo
-                    s.x += ue.x * xe.x + ue.y * xe.y + uo.x * xo.x + uo.y * xo.y;
-                    s.y += ue.x * xe.y - ue.y * xe.x + uo.x * xo.y - uo.y * xo.x;
+#pragma unroll
+                    for (int r = 0; r < RG; ++r) {
+                        if (r >= nr) break;  // uniform
+                        const float4 uu = uh[r * specs];
+                        float2 ue = make_float2(uu.x, uu.y), uo = make_float2(uu.z, uu.w);
+                        if constexpr (decltype(round)::value) {
+                            ue = bf16r2(ue);
+                            uo = bf16r2(uo);
+                        }
+                        // conj(ue) * xe + conj(uo) * xo
+                        s[i][r].x += ue.x * xe.x + ue.y * xe.y + uo.x * xo.x + uo.y * xo.y;
+                        s[i][r].y += ue.x * xe.y - ue.y * xe.x + uo.x * xo.y - uo.y * xo.x;
+                    }
                 }
-                Sacc[it] = s;
             }
         };
         if (bf16)
@@ -263,108 +283,192 @@ __device__ void align_pair_block(const PairJob &job, Geo g, int mode, int bf16, 
             dot(std::false_type{});
     }
     __syncthreads();
-    float2 *S = Z0;  // reuse
-    for (int w = threadIdx.x; w < Wn; w += NT) {
-        float2 s = make_float2(0.f, 0.f);
+    // the threads' sums through the FFT buffers: [r][gg][w]
+    float2 *Sacc = Z0;
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+        const int it = tid + i * NT;
+#pragma unroll
+        for (int r = 0; r < RG; ++r)
+            if (r < nr && it < items) Sacc[r * items + it] = s[i][r];
+    }
+    __syncthreads();
+    const float iW = __builtin_amdgcn_rcpf((float)Wn);
+    for (int x = tid; x < nr * Wn; x += NT) {
+        const int r = div_small(x, iW), w = x - __mul24(r, Wn);
+        float2 t = make_float2(0.f, 0.f);
         for (int gg = 0; gg < G; ++gg) {
-            s.x += Sacc[w * G + gg].x;
-            s.y += Sacc[w * G + gg].y;
+            const float2 v = Sacc[r * items + __mul24(gg, Wn) + w];
+            t.x += v.x;
+            t.y += v.y;
         }
-        S[w] = s;
+        S[r * (Wn + 1) + w] = t;
     }
     __syncthreads();
 
-    // --- inverse transform over w, translation correction, objective per lag
-    const double nq = (double)n * (double)Q;
-    for (int l = threadIdx.x; l < n; l += NT) {
-        float acc = S[0].x + ((l & 1) ? -S[n / 2].x : S[n / 2].x);
-        float part = 0.f;
-        int m = l;
-        for (int w = 1; w < n / 2; ++w) {
-            const float2 t = tw[m];
-            part += S[w].x * t.x + S[w].y * t.y;  // Re(S e^{+2 pi i w l / n})
+    // --- inverse transform over w.  Lags l and l + n/2 share every twiddle up
+    // to the sign (-1)^w, so one sum over even w and one over odd w gives both;
+    // the w range is cut in `parts` so that every thread has a share.
+    const int parts = min(8, max(1, NT / half)), len = (half - 1 + parts - 1) / parts;
+    float2 *ps = Z0;  // [parts][nr][half] (even, odd)
+    const float ih = __builtin_amdgcn_rcpf((float)half);
+    const float ir = __builtin_amdgcn_rcpf((float)nr);
+    for (int x = tid; x < parts * nr * half; x += NT) {
+        const int pr = div_small(x, ih), l = x - __mul24(pr, half);
+        const int part = div_small(pr, ir), r = pr - __mul24(part, nr);
+        const float2 *Sr = S + r * (Wn + 1);
+        const int w0 = 1 + part * len, w1 = min(w0 + len, half);
+        float ev = 0.f, od = 0.f;
+        int m = __mul24(w0, l);
+        m -= __mul24(div_small(m, 0.5f * ih), n);
+        for (int w = w0; w < w1; ++w) {
+            const float2 t = tw[m], v = Sr[w];
+            const float re = v.x * t.x + v.y * t.y;  // Re(S e^{+2 pi i w l / n})
+            if (w & 1) od += re;
+            else ev += re;
             m += l;
             if (m >= n) m -= n;
         }
-        const double Cl = ((double)acc + 2.0 * (double)part) / (double)n;
-        double d = (au[1] + av[1] - 2.0 * Cl) / nq;
-        if (mode == 0) {
-            const double2 b = trans_moment(au, av, tw64[l]);
-            d -= 2.0 * (b.x * b.x + b.y * b.y);
-        }
-        D[l] = d;
-        if (job.curve) job.curve[l] = (float)d;
+        ps[x] = make_float2(ev, od);
     }
     __syncthreads();
 
-    // --- top-K lags
-    const int K = top_k;
-    for (int c = 0; c < K; ++c) {
-        const int l = block_argmin<NT>(D, n, rv, ri);
-        if (threadIdx.x == 0) {
-            cand[c] = l;
-            D[l] = __builtin_inf();
+    // --- translation correction, objective per lag
+    const double nq = (double)n * (double)Q;
+    for (int x = tid; x < nr * half; x += NT) {
+        const int r = div_small(x, ih), l = x - __mul24(r, half);
+        const double *au = job.au + 4 * r;
+        float ev = 0.f, od = 0.f;
+        for (int part = 0; part < parts; ++part) {
+            const float2 v = ps[part * nr * half + x];
+            ev += v.x;
+            od += v.y;
         }
-        __syncthreads();
+        const float2 *Sr = S + r * (Wn + 1);
+        const float ends = Sr[0].x + ((l & 1) ? -Sr[half].x : Sr[half].x);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int lag = l + h * half;
+            const double Cl = ((double)ends + 2.0 * (double)(h ? ev - od : ev + od)) / (double)n;
+            double d = (au[1] + av[1] - 2.0 * Cl) / nq;
+            if (mode == 0) {
+                const double2 b = trans_moment(au, av, tw64[lag]);
+                d -= 2.0 * (b.x * b.x + b.y * b.y);
+            }
+            D[r * n + lag] = d;
+            if (job.curve && (live >> r & 1)) job.curve[r * job.stride * n + lag] = (float)d;
+        }
     }
+    __syncthreads();
 
-    // --- FP32 rescore of the candidates: direct residual sum
-    float sx[kMaxTopK], sy[kMaxTopK], part[kMaxTopK];
-    int lc[kMaxTopK];
+    // --- top-K lags of each reference, one wave per reference
+    for (int r = wave; r < nr; r += NW) {
+        double *Dr = D + r * n;
+        for (int c = 0; c < K; ++c) {
+            double v = __builtin_inf();
+            int i = 0x7fffffff;
+            for (int l = lane; l < n; l += 64) argmin_merge(v, i, Dr[l], l);
 #pragma unroll
-    for (int c = 0; c < kMaxTopK; ++c) {
-        lc[c] = c < K ? cand[c] : 0;
-        double2 b = make_double2(0.0, 0.0);
-        if (mode == 0 && c < K) b = trans_moment(au, av, tw64[lc[c]]);
-        sx[c] = (float)(2.0 * b.x);
-        sy[c] = (float)(2.0 * b.y);
-        part[c] = 0.f;
+            for (int off = 32; off >= 1; off >>= 1) {
+                const double v2 = __shfl_xor(v, off, 64);
+                const int i2 = __shfl_xor(i, off, 64);
+                argmin_merge(v, i, v2, i2);
+            }
+            if (i >= n) i = 0;  // every D* is NaN
+            if (lane == 0) {
+                Dr[i] = __builtin_inf();
+                double2 b = make_double2(0.0, 0.0);
+                if (mode == 0) b = trans_moment(job.au + 4 * r, av, tw64[i]);
+                lagS[r * K + c] = i;
+                shiftS[r * K + c] = make_float2((float)(2.0 * b.x), (float)(2.0 * b.y));
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
     }
-    // rows of V pass through LDS (the FFT buffers, free by now): every element
-    // is read once from memory and K times from LDS
+    __syncthreads();
+
+    // --- FP32 rescore of the candidates: direct residual sums, kAlignSlots of
+    // the nr K candidates at a time.  Rows of V pass through LDS (the FFT
+    // buffers, free by now): every element is read once from memory per batch
+    // of candidates and once per candidate from LDS.
     float *Vs = (float *)Z0;
-    const int RS = 4 * kFftElems / n;
-    for (int j0 = 0; j0 < Q; j0 += RS) {
-        const int cnt = min(RS, Q - j0) * n;
-        const float *Vg = V + (int64_t)j0 * n;
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < cnt; idx += NT) Vs[idx] = Vg[idx];
-        __syncthreads();
-        const float *Ug = U + (int64_t)j0 * n;
-        for (int idx = threadIdx.x; idx < cnt; idx += NT) {
-            const int jl = idx / n, k = idx - jl * n;
-            const float u = Ug[idx];
-            const float2 dk = tw[k];
-            const float *vrow = Vs + jl * n;
+    const int RS = 4 * kFftElems / n, slots = nr * K;
+    const float in = __builtin_amdgcn_rcpf((float)n), iK = __builtin_amdgcn_rcpf((float)K);
+    const int j_0 = div_small(tid, in), k_0 = tid - __mul24(j_0, n);
+    const int dk = NT % n;  // uniform
+    auto rescore = [&](auto count, int c0, int nb) {
+        constexpr int NB = decltype(count)::value;
+        float part[NB];
+        int lag[NB], ref[NB];
+        float2 sh[NB];
 #pragma unroll
-            for (int c = 0; c < kMaxTopK; ++c) {
-                if (c < K) {
-                    int kk = k + lc[c];
+        for (int c = 0; c < NB; ++c) {
+            const int q = c0 + min(c, nb - 1);  // slots past the last repeat it
+            part[c] = 0.f;
+            lag[c] = __builtin_amdgcn_readfirstlane(lagS[q]);
+            ref[c] = __builtin_amdgcn_readfirstlane(div_small(q, iK));
+            sh[c] = shiftS[q];
+        }
+        for (int j0 = 0; j0 < Q; j0 += RS) {
+            const int cnt = min(RS, Q - j0) * n;
+            const float *Vg = job.V + (int64_t)j0 * n;
+            __syncthreads();
+            for (int idx = tid; idx < cnt; idx += NT) Vs[idx] = Vg[idx];
+            __syncthreads();
+            const float *Ug = job.U + (int64_t)j0 * n;
+            int k = k_0;
+            for (int idx = tid; idx < cnt; idx += NT) {
+                const float2 d = tw[k];
+                const float *vrow = Vs + (idx - k);
+                float u = 0.f;
+#pragma unroll
+                for (int c = 0; c < NB; ++c) {
+                    if (c == 0 || ref[c] != ref[c - 1])  // uniform
+                        u = Ug[(int64_t)ref[c] * Q * n + idx];
+                    int kk = k + lag[c];
                     if (kk >= n) kk -= n;
-                    const float e = u - vrow[kk] - (sx[c] * dk.x + sy[c] * dk.y);
+                    const float e = u - vrow[kk] - (sh[c].x * d.x + sh[c].y * d.y);
                     part[c] += e * e;
                 }
+                k += dk;
+                if (k >= n) k -= n;
             }
         }
-    }
-    int best_l = 0;
-    float best = 0.f, bsx = 0.f, bsy = 0.f;
-    for (int c = 0; c < K; ++c) {
-        const float v = block_sum<NT>(part[c], rf) / (float)nq;
-        if (c == 0 || v < best || (v == best && lc[c] < best_l)) {
-            best = v;
-            best_l = lc[c];
-            bsx = sx[c];
-            bsy = sy[c];
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+            float v = part[c];
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+            if (lane == 0) red[wave][c] = v;
         }
+        __syncthreads();
+        if (tid < nb) {
+            float t = 0.f;
+            for (int w = 0; w < NW; ++w) t += red[w][tid];
+            valS[c0 + tid] = t / (float)nq;
+        }
+    };
+    for (int c0 = 0; c0 < slots; c0 += kAlignSlots) {
+        const int nb = min(kAlignSlots, slots - c0);
+        if (nb == 1) rescore(std::integral_constant<int, 1>{}, c0, nb);
+        else if (nb <= 4) rescore(std::integral_constant<int, 4>{}, c0, nb);
+        else rescore(std::integral_constant<int, 8>{}, c0, nb);
     }
-    if (threadIdx.x == 0) {
+    __syncthreads();
+    if (tid < nr && (live >> tid & 1)) {
+        const int r = tid;
+        int bc = r * K;
+        for (int c = bc + 1; c < r * K + K; ++c)
+            if (valS[c] < valS[bc] || (valS[c] == valS[bc] && lagS[c] < lagS[bc])) bc = c;
         const float L = (float)g.L;
-        res->rot_index = best_l;
-        res->theta_rad = (float)(6.283185307179586 * (double)best_l / (double)n);
-        res->shift_px[0] = bsx * 0.5f * L;
-        res->shift_px[1] = bsy * 0.5f * L;
-        res->sw2sq = best;
+        Result *res = job.res + r * job.stride;
+        res->rot_index = lagS[bc];
+        res->theta_rad = (float)(6.283185307179586 * (double)lagS[bc] / (double)n);
+        res->shift_px[0] = shiftS[bc].x * 0.5f * L;
+        res->shift_px[1] = shiftS[bc].y * 0.5f * L;
+        res->sw2sq = valS[bc];
         res->status = 0;
     }
 }

@@ -36,25 +36,39 @@ __device__ __forceinline__ void dft_small(float2 (&a)[R]) {
     }
 }
 
+// Quotient of small non-negative integers by d, given inv = 1 / d: the float
+// product is within q 2^-22 of (x + 1/2) / d, which lies at least 1 / (2 d) from
+// an integer, so the truncation is exact while x < 2^21.
+__device__ __forceinline__ int div_small(int x, float inv) {
+    return (int)(((float)x + 0.5f) * inv);
+}
+
 // One Stockham pass of radix R over `rows` complex rows of length n, from X
-// to Y (row stride n).  p = product of the radices already applied.
+// to Y (row stride n).  p = product of the radices already applied.  The
+// indices are quotients by n / R and by p, which integer division would make
+// most of the pass's instructions.
 template <int NT, int R>
-__device__ void fft_pass(const float2 *X, float2 *Y, int rows, int n, int p, const float2 *tw) {
+__device__ __forceinline__ void fft_pass(const float2 *X, float2 *Y, int rows, int n, int p,
+                                         const float2 *tw) {
     const int nr = n / R;
     const int nb = rows * nr;
     const int ts = n / (p * R);
+    const float inr = __builtin_amdgcn_rcpf((float)nr), ip = __builtin_amdgcn_rcpf((float)p);
     for (int idx = threadIdx.x; idx < nb; idx += NT) {
-        const int row = idx / nr, i = idx - row * nr;
-        const int k = i % p;
-        const float2 *x = X + row * n + i;
+        const int row = div_small(idx, inr), i = idx - __mul24(row, nr);
+        const int k = i - __mul24(div_small(i, ip), p);
+        const float2 *x = X + __mul24(row, n) + i;
         float2 v[R];
+        int m = 0;  // q k ts
+        const int dm = __mul24(k, ts);
 #pragma unroll
         for (int q = 0; q < R; ++q) {
             v[q] = x[q * nr];
-            if (q > 0) v[q] = cmul(v[q], tw[q * k * ts]);
+            if (q > 0) v[q] = cmul(v[q], tw[m]);
+            m += dm;
         }
         dft_small<R>(v);
-        float2 *y = Y + row * n + (i - k) * R + k;
+        float2 *y = Y + __mul24(row, n) + __mul24(i - k, R) + k;
 #pragma unroll
         for (int q = 0; q < R; ++q) y[q * p] = v[q];
     }

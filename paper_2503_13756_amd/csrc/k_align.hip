@@ -1,11 +1,13 @@
 // Kernels and launchers of the angle spectra and the per-pair alignment;
 // the device routines are in align_dev.h.
+#include <algorithm>
+
 #include "align_dev.h"
 
 namespace sw {
 
-// What the spectra of a table become: FP32 or packed bf16 complex spectra
-// spec[w][j], or the coefficients of the register-FFT alignment of n = 128
+// What the spectra of a table become: FP32 spectra (store_spectrum), packed
+// bf16 complex spectra spec[w][j], or the coefficients of the register-FFT alignment of n = 128
 // (gam, then gamx; see store_gamma128).
 enum SpectrumOut { kSpecF32, kSpecBf16, kSpecGamma };
 
@@ -28,13 +30,13 @@ __global__ __launch_bounds__(NT) void k_spectrum(const float *__restrict__ qt, i
     if constexpr (OUT == kSpecGamma) {
         float2 *gam = (float2 *)out + gi * P2 * kA128Slots;
         float2 *gx = (float2 *)out + N * P2 * kA128Slots + gi * P2 * 2;
-        spectrum_rows<NT>(T, g.n, pbeg, pend, CH, tw32, lds2,
+        spectrum_rows<NT, false>(T, g.n, pbeg, pend, CH, tw32, lds2,
                           [&](int p, int w, float2 xe, float2 xo) {
                               store_gamma128(gam, gx, p, w, xe, xo);
                           });
     } else if constexpr (OUT == kSpecBf16) {
         uint32_t *sp = (uint32_t *)out + gi * Wn * g.Q;
-        spectrum_rows<NT>(T, g.n, pbeg, pend, CH, tw32, lds2,
+        spectrum_rows<NT, true>(T, g.n, pbeg, pend, CH, tw32, lds2,
                           [&](int p, int w, float2 xe, float2 xo) {
                               const float2 e = bf16r2(xe), d = bf16r2(xo);
                               uint2 v;
@@ -45,40 +47,40 @@ __global__ __launch_bounds__(NT) void k_spectrum(const float *__restrict__ qt, i
                               *(uint2 *)(sp + (int64_t)w * g.Q + 2 * p) = v;
                           });
     } else {
-        float2 *sp = (float2 *)out + gi * Wn * g.Q;
-        spectrum_rows<NT>(T, g.n, pbeg, pend, CH, tw32, lds2,
+        float4 *sp = (float4 *)out + gi * Wn * P2;
+        spectrum_rows<NT, false>(T, g.n, pbeg, pend, CH, tw32, lds2,
                           [&](int p, int w, float2 xe, float2 xo) {
-                              store_spectrum(sp, g.Q, p, w, xe, xo);
+                              store_spectrum(sp, Wn, p, w, xe, xo);
                           });
     }
 }
 
-template <int NT>
-__global__ __launch_bounds__(NT) void k_align_pairs(PairArgs a, Geo g,
+// One block per image and run of `rg` references (all pairs), or per listed
+// pair (rg = 1).
+template <int NT, int RG>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(RG == 1 ? 7 : 5, 8))) void k_align_pairs(PairArgs a, Geo g, int rg,
                                                     const float2 *__restrict__ tw32,
                                                     const double2 *__restrict__ tw64) {
     extern __shared__ __align__(16) float2 lds2[];
     const int n = g.n, Q = g.Q, Wn = n / 2 + 1;
-    const int64_t pi = blockIdx.x;
-    const int64_t P = a.pairs ? a.n_pairs : a.n_ref * a.n_img;
-    if (pi >= P) return;
-    const int64_t r = a.pairs ? a.pairs[2 * pi] : pi / a.n_img;
-    const int64_t gi = a.pairs ? a.pairs[2 * pi + 1] : pi % a.n_img;
+    const int64_t b = blockIdx.x;
+    const int64_t r = a.pairs ? a.pairs[2 * b] : b / a.n_img * rg;
+    const int64_t gi = a.pairs ? a.pairs[2 * b + 1] : b % a.n_img;
     const bool in_range = r >= 0 && r < a.n_ref && gi >= 0 && gi < a.n_img;
-    PairJob job;
-    job.au = a.ref_aux + 4 * (in_range ? r : 0);
-    job.av = a.img_aux + 4 * (in_range ? gi : 0);
-    job.U = a.ref_qt + (in_range ? r : 0) * (int64_t)Q * n;
-    job.V = a.img_qt + (in_range ? gi : 0) * (int64_t)Q * n;
-    job.Uh = a.ref_spec + (in_range ? r : 0) * (int64_t)Wn * Q;
+    const int64_t rr = in_range ? r : 0, gg = in_range ? gi : 0;
+    const int64_t pi = a.pairs ? b : r * a.n_img + gi;
+    PairsJob job;
+    job.au = a.ref_aux + 4 * rr;
+    job.av = a.img_aux + 4 * gg;
+    job.U = a.ref_qt + rr * (int64_t)Q * n;
+    job.V = a.img_qt + gg * (int64_t)Q * n;
+    job.Uh = (const float4 *)a.ref_spec + rr * (int64_t)Wn * (Q / 2);
     job.res = a.out + pi;
     job.curve = a.curve ? a.curve + pi * n : nullptr;
-    int status = 0;
-    if (!in_range) status = 3;  // bad pair index
-    else if (isnan(job.au[0]) || isnan(job.av[0])) status = 2;
-    else if (!(job.au[0] > 0.0) || !(job.av[0] > 0.0)) status = 1;
-    job.status = status;
-    align_pair_block<NT>(job, g, a.mode, a.bf16, a.top_k, tw32, tw64, lds2);
+    job.stride = a.n_img;
+    job.nr = (int)min((int64_t)rg, a.n_ref - rr);
+    job.status = in_range ? 0 : 3;
+    align_pairs_block<NT, RG>(job, g, a.mode, a.bf16, a.top_k, tw32, tw64, lds2);
 }
 
 // Packed rows per block: one block per table, in chunks of kFftElems, when
@@ -113,19 +115,32 @@ hipError_t launch_gamma128(const float *qt, int64_t N, Geo g, const AngleTable &
     return launch_spectrum_t<kSpecGamma>(qt, N, g, t, gam, s);
 }
 
+template <int RG>
+static hipError_t launch_align_pairs_t(const PairArgs &a, Geo g, const AngleTable &t, int rg,
+                                       int64_t blocks, hipStream_t s) {
+    constexpr int NT = 256;
+    static const hipError_t attr = hipFuncSetAttribute(
+        (const void *)k_align_pairs<NT, RG>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+    (void)attr;
+    hipLaunchKernelGGL((k_align_pairs<NT, RG>), dim3((unsigned)blocks), dim3(NT),
+                       align_pairs_lds(g.n, RG), s, a, g, rg, t.d32, t.d64);
+    return hipGetLastError();
+}
+
+// References per block: as many as eight, as long as that leaves kAlignBlocks
+// blocks, four on every compute unit (fewer pairs are spread one by one).
+// n = 512 has more spectral sums than a block of several references holds.
+constexpr int64_t kAlignBlocks = 1024;
+
 hipError_t launch_align_pairs(const PairArgs &a, Geo g, const AngleTable &t, hipStream_t s) {
     const int64_t P = a.pairs ? a.n_pairs : a.n_ref * a.n_img;
     if (P <= 0) return hipSuccess;
-    constexpr int NT = 256;
-    const int Wn = g.n / 2 + 1;
-    const int G = Wn >= NT ? 1 : NT / Wn;
-    const size_t lds = sizeof(float2) * (g.n + 2 * kFftElems + Wn * G) + sizeof(double) * g.n;
-    static const hipError_t attr = hipFuncSetAttribute(
-        (const void *)k_align_pairs<NT>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-    (void)attr;
-    hipLaunchKernelGGL((k_align_pairs<NT>), dim3((unsigned)P), dim3(NT), lds, s, a, g, t.d32,
-                       t.d64);
-    return hipGetLastError();
+    int64_t rg = 1;
+    if (!a.pairs && g.n < 512)
+        rg = std::min({(int64_t)8, a.n_ref, std::max((int64_t)1, P / kAlignBlocks)});
+    if (rg == 1) return launch_align_pairs_t<1>(a, g, t, 1, P, s);
+    rg = (a.n_ref + (a.n_ref + rg - 1) / rg - 1) / ((a.n_ref + rg - 1) / rg);  // even runs
+    return launch_align_pairs_t<8>(a, g, t, (int)rg, (a.n_ref + rg - 1) / rg * a.n_img, s);
 }
 
 }  // namespace sw

@@ -34,7 +34,10 @@ __device__ __forceinline__ int64_t next_work(unsigned long long *counter, int64_
     __syncthreads();
     if (threadIdx.x == 0) *slot = (int64_t)atomicAdd(counter, 1ull);
     __syncthreads();
-    return *slot;
+    // made uniform, so that the item's fields are scalars
+    const unsigned long long w = (unsigned long long)*slot;
+    return (int64_t)(((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(w >> 32)) << 32) |
+                     (unsigned)__builtin_amdgcn_readfirstlane((unsigned)w));
 }
 
 // What the alignment of an item reads of its reference's table T: the
@@ -42,12 +45,15 @@ __device__ __forceinline__ int64_t next_work(unsigned long long *counter, int64_
 template <int NT>
 __device__ void reference_spectrum(const MixItem &it, const float *T, float2 *lds2) {
     const int Q = it.Q;
-    float2 *const gam = it.gam, *const spec = it.ref_spec;
-    spectrum_rows<NT>(T, it.n, 0, Q / 2, fft_chunk_rows(it.n, Q), it.d32, lds2,
-                      [&](int p, int w, float2 xe, float2 xo) {
-                          if (gam) store_gamma128(gam, gam + Q / 2 * kA128Slots, p, w, xe, xo);
-                          else store_spectrum(spec, Q, p, w, xe, xo);
-                      });
+    float2 *const gam = it.gam;
+    float4 *const spec = (float4 *)it.ref_spec;
+    const int Wn = it.n / 2 + 1;
+    spectrum_rows<NT, false>(
+        T, it.n, 0, Q / 2, fft_chunk_rows(it.n, Q), it.d32, lds2,
+        [&](int p, int w, float2 xe, float2 xo) {
+            if (gam) store_gamma128(gam, gam + Q / 2 * kA128Slots, p, w, xe, xo);
+            else store_spectrum(spec, Wn, p, w, xe, xo);
+        });
 }
 
 // Images -> quantile tables for every item of two groups: the work queue
@@ -168,32 +174,34 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
 }
 
 // Other items (work items [split, total)): LDS-FFT alignment of every image
-// against the item's reference.
+// against the item's reference.  Held to 72 VGPRs for seven waves per SIMD:
+// left alone the compiler takes 113 in the work loop, and the four waves that
+// leaves are slower (uneven stacks: 1.23 ms against 0.91 with 44 spills).
 template <int NT>
-__global__ __launch_bounds__(NT) void k_align_mixed(const MixGroup *__restrict__ G,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_align_mixed(const MixGroup *__restrict__ G,
                                                     unsigned long long *counter) {
     extern __shared__ __align__(16) float2 lds2[];
     __shared__ int64_t wslot;
     const int64_t total = G->total, split = G->split;
+    if (split >= total) return;  // every item has n = 128: not one queue access
     for (;;) {
         const int64_t w = split + next_work<NT>(counter, &wslot);
         if (w >= total) break;
         const MixItem &it = G->items[find_item(G, w)];
         const int64_t gi = w - it.first;
         Geo g{it.L, it.n, it.Q, it.levels};
-        PairJob job;
+        PairsJob job;
         job.U = it.ref_qt;
         job.au = it.ref_aux;
-        job.Uh = it.ref_spec;
+        job.Uh = (const float4 *)it.ref_spec;
         job.V = it.qt + gi * (int64_t)it.Q * it.n;
         job.av = it.aux + 4 * gi;
         job.res = it.out + gi;
         job.curve = nullptr;
-        int status = 0;
-        if (isnan(job.au[0]) || isnan(job.av[0])) status = 2;
-        else if (!(job.au[0] > 0.0) || !(job.av[0] > 0.0)) status = 1;
-        job.status = status;
-        align_pair_block<NT>(job, g, it.mode, it.bf16, it.top_k, it.d32, it.d64, lds2);
+        job.stride = 0;
+        job.nr = 1;
+        job.status = 0;
+        align_pairs_block<NT, 1>(job, g, it.mode, it.bf16, it.top_k, it.d32, it.d64, lds2);
     }
 }
 
@@ -226,10 +234,7 @@ MixLaunch plan_mixed(MixItem *items, int nitems, MixKnobs knobs) {
         if (!it.fused) slot = max(slot, (int64_t)pmf);
         lmax = max(lmax, it.L);
         nmax = max(nmax, it.n);
-        const int Wn = it.n / 2 + 1;
-        const int G = Wn >= NT ? 1 : NT / Wn;
-        align_lds = max(align_lds, sizeof(float2) * (it.n + 2 * kFftElems + Wn * G) +
-                                       sizeof(double) * it.n);
+        align_lds = max(align_lds, align_pairs_lds(it.n, 1));
     }
     region = (region + 1) & ~1;
     const size_t fixed = sizeof(float) * region + sizeof(double) * 2 * nmax;

@@ -21,7 +21,7 @@ struct MixItem {
     double *aux;        // [count][4]
     const float *ref_qt;
     const double *ref_aux;
-    float2 *ref_spec;   // [n/2+1][Q] FP32, written by the launch
+    float2 *ref_spec;   // [Q/2][n/2+1][2] FP32 (store_spectrum), written by the launch
     Result *out;        // [count]
     const float2 *d32;  // angle table of n
     const double2 *d64;

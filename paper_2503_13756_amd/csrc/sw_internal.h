@@ -127,8 +127,8 @@ bool tables_fused_fits(Geo g);
 hipError_t launch_tables(const float *img, int64_t N, Geo g, const AngleTable &t,
                          const ProjPlan &pp, float *qt, double *aux, hipStream_t s,
                          int per_block = 2);
-// Angle spectra of quantile tables: spec[g][w][j] complex, w in [0, n/2],
-// j in [0, Q); bf16 != 0 stores bfloat16 pairs instead of float pairs.
+// Angle spectra of quantile tables, w in [0, n/2]: bf16 != 0 stores spec[g][w][j],
+// j in [0, Q), as bfloat16 pairs; bf16 == 0 stores [g][j/2][w][j%2] float pairs.
 hipError_t launch_spectrum(const float *qt, int64_t N, Geo g, const AngleTable &t, void *spec,
                            int bf16, hipStream_t s);
 struct PairArgs {

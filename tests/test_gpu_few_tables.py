@@ -81,3 +81,41 @@ def test_small_batches_equal_large_ones(api, tmp_path, L, n, Q, N):
             ctx.close()
         assert np.array_equal(out["small"][0], out["large"][0]), ramp
         assert np.array_equal(out["small"][1], out["large"][1]), ramp
+
+
+# references per block of the FFT alignment: one (few pairs), runs of two to
+# eight with an uneven last run; n = 512 never shares; bf16 rescores four lags
+# of each reference, in batches of eight candidates
+@pytest.mark.parametrize("L,n,Q,refs,images", [(16, 16, 12, 3, 700), (39, 48, 48, 9, 300),
+                                               (24, 24, 20, 8, 1200), (40, 96, 44, 11, 200),
+                                               (64, 256, 24, 5, 500), (24, 512, 8, 4, 600)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_references_sharing_a_block(api, oracle, L, n, Q, refs, images, prec):
+    """All pairs of `refs` references and `images` images, whose blocks share an
+    image's transforms between references, against the listed pairs, one per
+    block, bit for bit (an empty image and a NaN reference among them), and
+    against the oracle on a sample."""
+    import torch
+    from tests import parity
+
+    _, imgs = synth.make_raw_stack(900 + L, L, 12)
+    imgs[5] = 0.0
+    imgs[1, L // 2, L // 2] = np.nan
+    ctx = api.Context(0)
+    q, a = api.tables(ctx, dev(imgs), n, Q)
+    ri = [k % 5 for k in range(refs)]  # references: tables 0..4
+    gi = [4 + k % 8 for k in range(images)]
+    rq, ra, iq, ia = (x[torch.tensor(k, device="cuda")].contiguous()
+                      for x, k in ((q, ri), (a, ri), (q, gi), (a, gi)))
+    res, curve = api.align_batch(ctx, rq, ra, iq, ia, L, prec=prec, want_curve=True)
+    pairs = np.array([(r, g) for r in range(refs) for g in range(images)], np.int64)
+    one, c1 = api.align_batch(ctx, rq, ra, iq, ia, L, prec=prec, want_curve=True, pairs=dev(pairs))
+    assert np.array_equal(res.cpu().numpy(), one.cpu().numpy())
+    assert np.array_equal(curve.cpu().numpy().view(np.uint32), c1.cpu().numpy().view(np.uint32))
+    s = np.r_[0:8, images:images + 8]
+    ok = [p for p in s if ri[p // images] != 1 and gi[p % images] != 5]
+    o = oracle.align(rq.cpu().numpy(), ra.cpu().numpy(), iq.cpu().numpy(), ia.cpu().numpy(), L,
+                     pairs=pairs[ok], want_curve=True)
+    g = api.unpack_results(res[torch.tensor(ok, device="cuda")])
+    parity.check(g, o, L, parity.TAU_BF16 if prec else parity.TAU_FP32, o["curve"])
+    ctx.close()
