@@ -20,7 +20,7 @@ enum SpectrumOut { kSpecF32, kSpecBf16, kSpecGamma };
 template <int NT, int OUT>
 __global__ __launch_bounds__(NT) void k_spectrum(const float *__restrict__ qt, int64_t N, Geo g,
                                                  const float2 *__restrict__ tw32, void *out,
-                                                 int rows, int CH) {
+                                                 int rows, int CH, float2 *norms) {
     extern __shared__ __align__(16) float2 lds2[];
     const int64_t gi = blockIdx.x;
     if (gi >= N) return;
@@ -36,6 +36,7 @@ __global__ __launch_bounds__(NT) void k_spectrum(const float *__restrict__ qt, i
                           });
     } else if constexpr (OUT == kSpecBf16) {
         uint32_t *sp = (uint32_t *)out + gi * Wn * g.Q;
+        float2 sq[kSpecNorms] = {};
         spectrum_rows<NT, true>(T, g.n, pbeg, pend, CH, tw32, lds2,
                           [&](int p, int w, float2 xe, float2 xo) {
                               const float2 e = bf16r2(xe), d = bf16r2(xo);
@@ -45,7 +46,43 @@ __global__ __launch_bounds__(NT) void k_spectrum(const float *__restrict__ qt, i
                               v.y = (__float_as_uint(d.x) >> 16) |
                                     (__float_as_uint(d.y) & 0xffff0000u);
                               *(uint2 *)(sp + (int64_t)w * g.Q + 2 * p) = v;
+                              const float2 t = lds2[w];  // e^{-2 pi i w / n}
+                              const float cw = w == 0 ? 0.f : w == Wn - 1 ? 1.f : 2.f;
+                              const float ex = xe.x - e.x, ey = xe.y - e.y, dx = xo.x - d.x,
+                                          dy = xo.y - d.y;
+                              const float a =
+                                  cw * (xe.x * xe.x + xe.y * xe.y + xo.x * xo.x + xo.y * xo.y);
+                              const float b = cw * (ex * ex + ey * ey + dx * dx + dy * dy);
+                              const float gw[kSpecNorms] = {2.f, sqrtf(2.f - 2.f * t.x),
+                                                            2.f * fabsf(t.y)};
+#pragma unroll
+                              for (int i = 0; i < kSpecNorms; ++i) {
+                                  sq[i].x += gw[i] * a;
+                                  sq[i].y += gw[i] * b;
+                              }
                           });
+        // this block's share of the squared norms (kSpecNorms)
+        if (norms) {  // uniform
+            __shared__ float2 ws[NT / 64][kSpecNorms];
+#pragma unroll
+            for (int i = 0; i < kSpecNorms; ++i) {
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) {
+                    sq[i].x += __shfl_xor(sq[i].x, off, 64);
+                    sq[i].y += __shfl_xor(sq[i].y, off, 64);
+                }
+                if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6][i] = sq[i];
+            }
+            __syncthreads();
+            if (threadIdx.x < kSpecNorms) {
+                float2 v = ws[0][threadIdx.x];
+                for (int w = 1; w < NT / 64; ++w) {
+                    v.x += ws[w][threadIdx.x].x;
+                    v.y += ws[w][threadIdx.x].y;
+                }
+                norms[(gi * gridDim.y + blockIdx.y) * kSpecNorms + threadIdx.x] = v;
+            }
+        }
     } else {
         float4 *sp = (float4 *)out + gi * Wn * P2;
         spectrum_rows<NT, false>(T, g.n, pbeg, pend, CH, tw32, lds2,
@@ -88,31 +125,39 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(RG == 1 ? 7 
 // one) for fewer tables, about kSpectrumBlocks blocks in all.
 constexpr int kSpectrumBlocks = 512;
 
+static int spectrum_rows_per_block(int64_t N, int P2) {
+    const int64_t want = N < kSpectrumBlocks ? (kSpectrumBlocks + N - 1) / N : 1;
+    return want >= P2 ? 1 : (int)((P2 + want - 1) / want);
+}
+
+int spectrum_blocks(int64_t N, Geo g) {
+    const int rows = spectrum_rows_per_block(N, g.Q / 2);
+    return (g.Q / 2 + rows - 1) / rows;
+}
+
 template <int OUT>
 static hipError_t launch_spectrum_t(const float *qt, int64_t N, Geo g, const AngleTable &t,
-                                    void *out, hipStream_t s) {
+                                    void *out, float2 *norms, hipStream_t s) {
     if (N <= 0) return hipSuccess;
     constexpr int NT = 256;
-    const int P2 = g.Q / 2;
-    const int64_t want = N < kSpectrumBlocks ? (kSpectrumBlocks + N - 1) / N : 1;
-    const int rows = want >= P2 ? 1 : (int)((P2 + want - 1) / want);
+    const int rows = spectrum_rows_per_block(N, g.Q / 2);
     int CH = kFftElems / g.n;
     if (CH > rows) CH = rows;
     const size_t lds = sizeof(float2) * (size_t)(g.n + 2 * CH * g.n);
-    hipLaunchKernelGGL((k_spectrum<NT, OUT>), dim3((unsigned)N, (unsigned)((P2 + rows - 1) / rows)),
-                       dim3(NT), lds, s, qt, N, g, t.d32, out, rows, CH);
+    hipLaunchKernelGGL((k_spectrum<NT, OUT>), dim3((unsigned)N, (unsigned)spectrum_blocks(N, g)),
+                       dim3(NT), lds, s, qt, N, g, t.d32, out, rows, CH, norms);
     return hipGetLastError();
 }
 
 hipError_t launch_spectrum(const float *qt, int64_t N, Geo g, const AngleTable &t, void *spec,
-                           int bf16, hipStream_t s) {
-    return bf16 ? launch_spectrum_t<kSpecBf16>(qt, N, g, t, spec, s)
-                : launch_spectrum_t<kSpecF32>(qt, N, g, t, spec, s);
+                           int bf16, hipStream_t s, float2 *norms) {
+    return bf16 ? launch_spectrum_t<kSpecBf16>(qt, N, g, t, spec, norms, s)
+                : launch_spectrum_t<kSpecF32>(qt, N, g, t, spec, nullptr, s);
 }
 
 hipError_t launch_gamma128(const float *qt, int64_t N, Geo g, const AngleTable &t, float2 *gam,
                            hipStream_t s) {
-    return launch_spectrum_t<kSpecGamma>(qt, N, g, t, gam, s);
+    return launch_spectrum_t<kSpecGamma>(qt, N, g, t, gam, nullptr, s);
 }
 
 template <int RG>

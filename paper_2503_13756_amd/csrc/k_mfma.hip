@@ -20,7 +20,12 @@
 // s of the residual with the shift s.d_k removed from every column (the same
 // algebra as the correction above, using sum_k d_k d_k^T = (n/2) I).  Image
 // tables sit in registers while reference tables stream through LDS as four
-// rotated copies, so every lag is a run of aligned 16-byte LDS reads.
+// rotated copies, so every lag is a run of aligned 16-byte LDS reads.  A
+// residual is 4,096 subtractions and multiply-adds at n = 64, and four of them
+// a pair were nine tenths of the call; k_corr_mfma therefore drops the
+// candidates that its estimate and the rounding errors of the bf16 spectra
+// prove not to be the minimum (1.24 of 4 are left on noisy copies of one
+// object): 2,000 x 2,000 at L = 64 5.44 -> 2.54 ms.
 #include "sw_internal.h"
 
 namespace sw {
@@ -47,6 +52,8 @@ __global__ __launch_bounds__(256) void k_corr_mfma(const uint32_t *__restrict__ 
                                                    int top_k, const double *__restrict__ ref_aux,
                                                    const double *__restrict__ img_aux,
                                                    const float2 *__restrict__ tw32,
+                                                   const float2 *__restrict__ norm_ref, int nb_ref,
+                                                   const float2 *__restrict__ norm_img, int nb_img,
                                                    int16_t *__restrict__ cand, int slice) {
     constexpr int Wn = N / 2 + 1;
     constexpr int SS = 2 * Wn + 1;  // odd LDS row stride
@@ -64,6 +71,23 @@ __global__ __launch_bounds__(256) void k_corr_mfma(const uint32_t *__restrict__ 
     if (it * 16 >= n_img) return;  // block-uniform, before any barrier
     const int64_t g0 = it * 16, r0 = rt * 16;
     for (int i = threadIdx.x; i < N; i += 256) tw[i] = tw32[i];
+    // norms of the tile's spectra (references, then images) for the pruning
+    __shared__ float2 nrm[32][kSpecNorms];
+    if (norm_ref && threadIdx.x < 32 * kSpecNorms) {
+        const int e = threadIdx.x / kSpecNorms, j = threadIdx.x - kSpecNorms * e;
+        const bool ref = e < 16;
+        const int64_t k = ref ? r0 + e : g0 + e - 16;
+        const float2 *src = ref ? norm_ref : norm_img;
+        const int nb = ref ? nb_ref : nb_img;
+        float2 q = make_float2(0.f, 0.f);
+        if (k < (ref ? n_ref : n_img))
+            for (int i = 0; i < nb; ++i) {
+                const float2 v = src[(k * nb + i) * kSpecNorms + j];
+                q.x += v.x;
+                q.y += v.y;
+            }
+        nrm[e][j] = make_float2(sqrtf(q.x), sqrtf(q.y));
+    }
 
     // Spectral products on the gfx950 bf16 MFMA with 32 K entries (16
     // complex values) per instruction: lane l holds row l % 16 (reference)
@@ -242,8 +266,52 @@ __global__ __launch_bounds__(256) void k_corr_mfma(const uint32_t *__restrict__ 
             top[c] = lo;
         }
     }
+    // Candidates that cannot win leave the list.  The difference of two lags'
+    // X differs from that of the exact spectra by at most
+    //   (1/n) sum_w c_w g_w sum_j |dU| |V| + |U| |dV| + |dU| |dV|,  w >= 1,
+    // dU = U^ - bf16(U^), g_w = |e^{2 pi i w l / n} - e^{2 pi i w l' / n}| (w = 0 is
+    // common to all lags), which Cauchy-Schwarz bounds by the tables' norms
+    // weighted with g (kSpecNorms: any lags, neighbours, two apart; the
+    // candidates mostly are neighbours, where g is small at the low
+    // frequencies that hold most of the energy).  The FP32 sums of X (fewer
+    // than 160 roundings of at most E = (E_U + E_V) / 2 each), the split operands
+    // of the inverse transform (3 2^-18 of the terms with w >= 1) and the
+    // rescore's own rounding come to less than kSum E + kSplit |U| |V| / n a lag.
+    // A candidate further below the largest X than that has a larger rescored
+    // objective for certain: the results are those of rescoring all top_k.
+    int keep = top_k;
+    if (norm_ref) {
+        constexpr float kSum = 1e-5f, kSplit = 2e-5f;
+        const float2 *a = nrm[t / 16], *v = nrm[16 + t % 16];
+        const float E = 0.5f * (float)(ref_aux[4 * r + 1] + img_aux[4 * g + 1]);
+        const float fix = 2.f * (kSum * E + kSplit / (float)N * a[0].x * v[0].x);
+        float T[kSpecNorms];
+#pragma unroll
+        for (int j = 0; j < kSpecNorms; ++j)
+            T[j] = fix + 1.001f / (float)N *
+                             (a[j].y * v[j].x + a[j].x * v[j].y + a[j].y * v[j].y);
+        float xs[KMAX], best = -__builtin_inff();
+        int lb = 0;
+#pragma unroll
+        for (int c = 0; c < KMAX; ++c) {
+            const int l = (int)(top[c] & (uint32_t)(N - 1));
+            xs[c] = Crow[l];
+            if (c < top_k && xs[c] > best) {
+                best = xs[c];
+                lb = l;
+            }
+        }
+        keep = 1;
+#pragma unroll
+        for (int c = 1; c < KMAX; ++c) {
+            const int d = ((int)(top[c] & (uint32_t)(N - 1)) - lb) & (N - 1);
+            const float Tc = d == 1 || d == N - 1 ? T[1] : d == 2 || d == N - 2 ? T[2] : T[0];
+            if (c < top_k && !(best - xs[c] > Tc)) keep = c + 1;  // NaN: kept
+        }
+    }
     int16_t *out = cand + (r * n_img + g) * (int64_t)top_k;
-    for (int c = 0; c < top_k; ++c) out[c] = (int16_t)(top[c] & (uint32_t)(N - 1));
+    for (int c = 0; c < top_k; ++c)
+        out[c] = c < keep ? (int16_t)(top[c] & (uint32_t)(N - 1)) : (int16_t)-1;
 }
 
 // Sum over the 64 lanes: butterflies inside each row of 16 lanes on DPP,
@@ -272,9 +340,14 @@ __device__ __forceinline__ float wave_sum_f(float v) {
 // four rotated copies C_s[j][i] = U[j][(i - s) mod N], s = 0..3: the lag
 // l = 4a + s pairs the lane's chunk with the aligned 16 bytes
 // C_s[j][4((p - a) mod CPR) ..], one conflict-free b128 read per four
-// elements at a fixed offset per row step.  Lane c < top_k carries candidate
-// c (its lag, translation and objective); the next reference's table and
-// candidates are fetched into registers while this one is summed.
+// elements at a fixed offset per row step.  Two sets of copies: the next
+// reference is staged while slower waves still sum the current one, with one
+// barrier per reference.
+//
+// The bookkeeping is lane-parallel over 16 references at a time: lane 4 b + c
+// carries candidate c of reference rb + b (its lag, -1 when pruned, its
+// residual, translation and objective), so that the double-precision part of
+// a pair costs a sixteenth of a wave's instructions.
 template <int N, int KMAX, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_rescore_tiles(
     const float *__restrict__ ref_qt, const double *__restrict__ ref_aux, int64_t n_ref,
@@ -283,8 +356,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     Result *__restrict__ out) {
     constexpr int Q = N, CPR = N / 4, RPS = 64 / CPR, STEPS = Q / RPS;
     constexpr int COPY = Q * N, NCH = Q * N / 4, CH = (NCH + NT - 1) / NT;
-    static_assert(KMAX <= 64 && STEPS * RPS == Q, "rescore layout");
-    extern __shared__ __align__(16) float lds[];  // [4][Q][N]
+    constexpr int RB = 64 / KMAX;  // references per batch of bookkeeping
+    static_assert(KMAX == 4 && STEPS * RPS == Q, "rescore layout");
+    extern __shared__ __align__(16) float lds[];  // [2][4][Q][N]
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int64_t g = (int64_t)blockIdx.x * (NT / 64) + wave;
     const bool live = g < n_img;  // wave-uniform
@@ -292,6 +366,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     const int64_t r0 = (int64_t)blockIdx.y * TR;
     const int64_t r1 = min(r0 + (int64_t)TR, n_ref);
     const int p = lane % CPR, jr = lane / CPR;
+    const int myc = lane % KMAX, myb = lane / KMAX;
     float4 vv[STEPS];
     {
         const float *V = img_qt + gc * (int64_t)COPY;
@@ -306,7 +381,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     // group to their left (same row, cyclic)
     constexpr bool kRor = CPR == 16;
     float4 ucur[CH], uprev[kRor ? 1 : CH];
-    int lnext = 0;
     auto fetch = [&](int64_t r) {
         const float4 *U = (const float4 *)(ref_qt + r * (int64_t)COPY);
 #pragma unroll
@@ -320,93 +394,108 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
                 }
             }
         }
-        lnext = lane < top_k ? (int)cand[(r * n_img + gc) * top_k + lane] : 0;
+    };
+    // lag of candidate myc of reference rb + myb (-1: none)
+    auto lags = [&](int64_t rb) {
+        const int64_t r = rb + myb;
+        return r < r1 && myc < top_k ? (int)cand[(r * n_img + gc) * top_k + myc] : -1;
     };
     if (r0 < r1) fetch(r0);
-    for (int64_t r = r0; r < r1; ++r) {
+    int lnext = lags(r0);
+    for (int64_t rb = r0; rb < r1; rb += RB) {
         const int lmine = lnext;
-        const double au0 = ref_aux[4 * r], au1 = ref_aux[4 * r + 2], au2 = ref_aux[4 * r + 3];
-        __syncthreads();  // every wave is done with the previous table
+        lnext = lags(rb + RB);
+        const uint64_t have = __ballot(lmine >= 0);
+        float sc = 0.f;  // residual of this lane's candidate
+        const int nr = (int)min((int64_t)RB, r1 - rb);
+        for (int b = 0; b < nr; ++b) {
+            const int64_t r = rb + b;
+            float *buf = lds + (int)((r - r0) & 1) * 4 * COPY;
+            // the set of copies written here was last read two references ago,
+            // before the previous barrier
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const int c = t + NT * i;
-            if (c < NCH) {
-                const float4 u = ucur[i];
-                float4 v;
-                if constexpr (kRor) {
-                    // chunk q - 1 (mod 16) of the same row sits one lane down
-                    // in this DPP row: row_ror:1
-                    v.x = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u.x), 0x121, 0xf, 0xf, false));
-                    v.y = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u.y), 0x121, 0xf, 0xf, false));
-                    v.z = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u.z), 0x121, 0xf, 0xf, false));
-                    v.w = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u.w), 0x121, 0xf, 0xf, false));
-                } else {
-                    v = uprev[i];
+            for (int i = 0; i < CH; ++i) {
+                const int c = t + NT * i;
+                if (c < NCH) {
+                    const float4 u = ucur[i];
+                    float4 v;
+                    if constexpr (kRor) {
+                        // chunk q - 1 (mod 16) of the same row sits one lane down
+                        // in this DPP row: row_ror:1
+                        v.x = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u.x), 0x121, 0xf, 0xf, false));
+                        v.y = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u.y), 0x121, 0xf, 0xf, false));
+                        v.z = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u.z), 0x121, 0xf, 0xf, false));
+                        v.w = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u.w), 0x121, 0xf, 0xf, false));
+                    } else {
+                        v = uprev[i];
+                    }
+                    float *d = buf + 4 * c;
+                    *(float4 *)(d) = u;
+                    *(float4 *)(d + COPY) = make_float4(v.w, u.x, u.y, u.z);
+                    *(float4 *)(d + 2 * COPY) = make_float4(v.z, v.w, u.x, u.y);
+                    *(float4 *)(d + 3 * COPY) = make_float4(v.y, v.z, v.w, u.x);
                 }
-                float *d = lds + 4 * c;
-                *(float4 *)(d) = u;
-                *(float4 *)(d + COPY) = make_float4(v.w, u.x, u.y, u.z);
-                *(float4 *)(d + 2 * COPY) = make_float4(v.z, v.w, u.x, u.y);
-                *(float4 *)(d + 3 * COPY) = make_float4(v.y, v.z, v.w, u.x);
+            }
+            __syncthreads();
+            if (r + 1 < r1) fetch(r + 1);
+            if (!live) continue;  // wave-uniform, after the barrier
+            const int nc = __builtin_popcount((unsigned)(have >> (KMAX * b)) & ((1u << KMAX) - 1));
+#pragma unroll 1
+            for (int c = 0; c < nc; ++c) {
+                const int l = __builtin_amdgcn_readlane(lmine, KMAX * b + c);
+                const float *src = buf + (l & 3) * COPY + jr * N + 4 * ((p - (l >> 2)) & (CPR - 1));
+                float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+                // reads run PIPE row steps ahead of the arithmetic
+                constexpr int PIPE = STEPS < 4 ? STEPS : 4;
+                float4 ub[STEPS];
+#pragma unroll
+                for (int m = 0; m < PIPE; ++m) ub[m] = *(const float4 *)(src + m * RPS * N);
+#pragma unroll
+                for (int m = 0; m < STEPS; ++m) {
+                    if (m + PIPE < STEPS)
+                        ub[m + PIPE] = *(const float4 *)(src + (m + PIPE) * RPS * N);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const float4 u = ub[m];
+                    const float4 v = vv[m];
+                    const float e0 = u.x - v.x, e1 = u.y - v.y, e2 = u.z - v.z, e3 = u.w - v.w;
+                    a0 = fmaf(e0, e0, a0);
+                    a1 = fmaf(e1, e1, a1);
+                    a2 = fmaf(e2, e2, a2);
+                    a3 = fmaf(e3, e3, a3);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const float sum = wave_sum_f((a0 + a1) + (a2 + a3));
+                if (lane == KMAX * b + c) sc = sum;
             }
         }
-        __syncthreads();
-        if (r + 1 < r1) fetch(r + 1);
-        if (!live) continue;  // wave-uniform, after both barriers
-        // translation at this lane's candidate lag (mode 0), Sec. 2.3
+        if (!live) continue;
+        // translation and objective at this lane's candidate (mode 0), Sec. 2.3
+        const int64_t rl = min(rb + myb, r1 - 1);
+        const double *au = ref_aux + 4 * rl;
         double bx = 0.0, by = 0.0;
         if (mode == 0) {
-            const double2 d = tw64[lmine];
+            const double2 d = tw64[max(lmine, 0)];
             const double cs = d.x, sn = -d.y;
-            bx = au1 - (cs * av1 - sn * av2);
-            by = au2 - (sn * av1 + cs * av2);
-        }
-        // lane c takes candidate c's residual
-        float sc = 0.f;
-#pragma unroll 1
-        for (int c = 0; c < KMAX; ++c) {
-            if (c >= top_k) break;
-            const int l = __builtin_amdgcn_readlane(lmine, c);
-            const float *src = lds + (l & 3) * COPY + jr * N + 4 * ((p - (l >> 2)) & (CPR - 1));
-            float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-            // reads run PIPE row steps ahead of the arithmetic
-            constexpr int PIPE = STEPS < 4 ? STEPS : 4;
-            float4 ub[STEPS];
-#pragma unroll
-            for (int m = 0; m < PIPE; ++m) ub[m] = *(const float4 *)(src + m * RPS * N);
-#pragma unroll
-            for (int m = 0; m < STEPS; ++m) {
-                if (m + PIPE < STEPS) ub[m + PIPE] = *(const float4 *)(src + (m + PIPE) * RPS * N);
-                __builtin_amdgcn_sched_barrier(0);
-                const float4 u = ub[m];
-                const float4 v = vv[m];
-                const float e0 = u.x - v.x, e1 = u.y - v.y, e2 = u.z - v.z, e3 = u.w - v.w;
-                a0 = fmaf(e0, e0, a0);
-                a1 = fmaf(e1, e1, a1);
-                a2 = fmaf(e2, e2, a2);
-                a3 = fmaf(e3, e3, a3);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const float sum = wave_sum_f((a0 + a1) + (a2 + a3));
-            if (lane == c) sc = sum;
+            bx = au[2] - (cs * av1 - sn * av2);
+            by = au[3] - (sn * av1 + cs * av2);
         }
         const float D = (float)((double)sc / nq - 2.0 * (bx * bx + by * by));
-        // smallest objective, ties to the smaller lag
-        int bc = 0;
-        float bd = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(D), 0));
-        int bl = __builtin_amdgcn_readlane(lmine, 0);
+        // smallest objective of the reference's candidates, ties to the smaller
+        // lag; the first candidate is never pruned
+        int bc = 0, bl = __shfl(lmine, KMAX * myb, 64);
+        float bd = __shfl(D, KMAX * myb, 64);
 #pragma unroll
         for (int c = 1; c < KMAX; ++c) {
-            if (c >= top_k) break;
-            const float dc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(D), c));
-            const int lc = __builtin_amdgcn_readlane(lmine, c);
-            if (dc < bd || (dc == bd && lc < bl)) {
+            const float dc = __shfl(D, KMAX * myb + c, 64);
+            const int lc = __shfl(lmine, KMAX * myb + c, 64);
+            if (lc >= 0 && (dc < bd || (dc == bd && lc < bl))) {
                 bd = dc;
                 bl = lc;
                 bc = c;
             }
         }
-        if (lane == bc) {
+        if (myc == bc && rb + myb < r1) {
+            const double au0 = au[0];
             int st = 0;
             if (isnan(au0) || isnan(av0)) st = 2;
             else if (!(au0 > 0.0) || !(av0 > 0.0)) st = 1;
@@ -424,7 +513,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
                 res.shift_px[1] = (float)(by * (double)L);
                 res.sw2sq = bd;
             }
-            out[r * n_img + g] = res;
+            out[(rb + myb) * n_img + g] = res;
         }
     }
 }
@@ -434,7 +523,8 @@ bool mfma_path_supported(Geo g) { return g.Q == g.n && (g.n == 32 || g.n == 64);
 // Threads of a rescore block: one image per wave against each staged
 // reference table, so 16 images share each staging of the four rotated
 // copies (64 KiB of LDS at n = 64, one block per CU either way); 2,000 x
-// 2,000 at L = 64: 5.35 ms with 512 threads, 5.27 ms with 1024.
+// 2,000 at L = 64, all four candidates of every pair: 5.35 ms with 512 threads,
+// 5.27 ms with 1024.
 constexpr int kRescoreThreads = 1024;
 
 template <int N>
@@ -452,7 +542,8 @@ static hipError_t launch_mfma_t(const MfmaArgs &a, Geo g, const AngleTable &t, h
     if (nblocks > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_corr_mfma<N, KMAX>), dim3((unsigned)nblocks), dim3(256), lds1, s,
                        a.spec_ref, a.spec_img, a.n_ref, a.n_img, g.Q, a.mode, a.top_k, a.ref_aux,
-                       a.img_aux, t.d32, a.cand, (int)slice);
+                       a.img_aux, t.d32, a.norm_ref, a.nb_ref, a.norm_img, a.nb_img, a.cand,
+                       (int)slice);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // blocks of NT / 64 images x TR references; TR chosen so that the grid
@@ -460,12 +551,12 @@ static hipError_t launch_mfma_t(const MfmaArgs &a, Geo g, const AngleTable &t, h
     constexpr int NT = kRescoreThreads, IPB = NT / 64;
     static const int slots = [] {
         (void)hipFuncSetAttribute((const void *)k_rescore_tiles<N, KMAX, NT>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 4 * N * N * 4);
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, 8 * N * N * 4);
         int dev = 0, cus = 0, per = 0;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per, (const void *)k_rescore_tiles<N, KMAX, NT>, NT, sizeof(float) * 4 * N * N);
+            &per, (const void *)k_rescore_tiles<N, KMAX, NT>, NT, sizeof(float) * 8 * N * N);
         return (cus > 0 ? cus : 256) * (per > 0 ? per : 1);
     }();
     const int64_t gx = (a.n_img + IPB - 1) / IPB;
@@ -482,7 +573,7 @@ static hipError_t launch_mfma_t(const MfmaArgs &a, Geo g, const AngleTable &t, h
     }
     const int TR = (int)((a.n_ref + best_gy - 1) / best_gy);
     const int gy = (int)((a.n_ref + TR - 1) / TR);
-    const size_t lds2 = sizeof(float) * 4 * N * N;
+    const size_t lds2 = sizeof(float) * 8 * N * N;
     hipLaunchKernelGGL((k_rescore_tiles<N, KMAX, NT>), dim3((unsigned)gx, (unsigned)gy), dim3(NT), lds2, s, a.ref_qt,
                        a.ref_aux, a.n_ref, a.img_qt, a.img_aux, a.n_img, TR, a.mode, a.top_k, g.L,
                        a.cand, t.d64, a.out);

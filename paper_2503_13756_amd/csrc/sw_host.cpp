@@ -1380,16 +1380,30 @@ static sw_status align_batch_impl(void *ctx, const sw_batch *b, sw_result *out, 
         const size_t per = sizeof(uint32_t) * (size_t)Wn * geo.Q;
         const size_t ref_bytes = (per * (size_t)b->n_ref + 255) & ~(size_t)255;
         const size_t img_bytes = same_set ? 0 : (per * (size_t)b->n_img + 255) & ~(size_t)255;
-        const size_t cand_bytes = sizeof(int16_t) * (size_t)P * top_k;
+        const size_t cand_bytes = (sizeof(int16_t) * (size_t)P * top_k + 255) & ~(size_t)255;
+        // the norms that prune candidates come on top; a no-alloc call that
+        // they would push over its limit rescores every candidate instead
+        const int nb_ref = sw::spectrum_blocks(b->n_ref, geo);
+        const int nb_img = same_set ? nb_ref : sw::spectrum_blocks(b->n_img, geo);
+        const size_t nref_bytes = (sizeof(float2) * sw::kSpecNorms * (size_t)b->n_ref * nb_ref + 255) & ~(size_t)255;
+        const size_t nimg_bytes = same_set ? 0 : sizeof(float2) * sw::kSpecNorms * (size_t)b->n_img * nb_img;
+        const size_t need = ref_bytes + img_bytes + sizeof(int16_t) * (size_t)P * top_k;
+        const size_t with_norms = ref_bytes + img_bytes + cand_bytes + nref_bytes + nimg_bytes;
+        const bool prune = !noalloc || with_norms <= kNoAllocWorkBytes;
         void *scr;
-        if ((st = take_scratch(ref_bytes + img_bytes + cand_bytes, &scr)) != SW_OK) return st;
+        if ((st = take_scratch(prune ? with_norms : need, &scr)) != SW_OK) return st;
         char *base = (char *)scr;
         uint32_t *spec_ref = (uint32_t *)base;
         uint32_t *spec_img = same_set ? spec_ref : (uint32_t *)(base + ref_bytes);
         int16_t *cand = (int16_t *)(base + ref_bytes + img_bytes);
-        hipError_t e = sw::launch_spectrum(b->ref_qt, b->n_ref, geo, *t, spec_ref, 1, s);
+        float2 *norm_ref =
+            prune ? (float2 *)(base + ref_bytes + img_bytes + cand_bytes) : nullptr;
+        float2 *norm_img =
+            !prune || same_set ? norm_ref
+                               : (float2 *)(base + ref_bytes + img_bytes + cand_bytes + nref_bytes);
+        hipError_t e = sw::launch_spectrum(b->ref_qt, b->n_ref, geo, *t, spec_ref, 1, s, norm_ref);
         if (e == hipSuccess && !same_set)
-            e = sw::launch_spectrum(b->img_qt, b->n_img, geo, *t, spec_img, 1, s);
+            e = sw::launch_spectrum(b->img_qt, b->n_img, geo, *t, spec_img, 1, s, norm_img);
         if (e != hipSuccess) return hip_fail(e, "k_spectrum launch");
         sw::MfmaArgs m;
         m.spec_ref = spec_ref;
@@ -1402,6 +1416,10 @@ static sw_status align_batch_impl(void *ctx, const sw_batch *b, sw_result *out, 
         m.n_img = b->n_img;
         m.mode = b->mode;
         m.top_k = top_k;
+        m.norm_ref = norm_ref;
+        m.norm_img = norm_img;
+        m.nb_ref = nb_ref;
+        m.nb_img = nb_img;
         m.cand = cand;
         m.out = (sw::Result *)out;
         e = sw::launch_mfma_all_pairs(m, geo, *t, s);

@@ -129,8 +129,15 @@ hipError_t launch_tables(const float *img, int64_t N, Geo g, const AngleTable &t
                          int per_block = 2);
 // Angle spectra of quantile tables, w in [0, n/2]: bf16 != 0 stores spec[g][w][j],
 // j in [0, Q), as bfloat16 pairs; bf16 == 0 stores [g][j/2][w][j%2] float pairs.
+// norms (bf16 only, nullable): [N][spectrum_blocks()][kSpecNorms] partial sums
+// over the frequencies 1 .. n/2 of g c_w |U^|^2 and g c_w |U^ - bf16(U^)|^2,
+// c_w = 2, 1 at n/2, with g = 2, 2 sin(pi w / n) and 2 |sin(2 pi w / n)|: the
+// largest |e^{i a} - e^{i b}| for any two lags, for neighbours and for lags two
+// apart.
+constexpr int kSpecNorms = 3;
+int spectrum_blocks(int64_t N, Geo g);
 hipError_t launch_spectrum(const float *qt, int64_t N, Geo g, const AngleTable &t, void *spec,
-                           int bf16, hipStream_t s);
+                           int bf16, hipStream_t s, float2 *norms = nullptr);
 struct PairArgs {
     const float *ref_qt;
     const double *ref_aux;
@@ -172,6 +179,8 @@ struct MfmaArgs {
     const double *img_aux;
     int64_t n_img;
     int mode, top_k;
+    const float2 *norm_ref, *norm_img;  // partial norms of the spectra, or null: no pruning
+    int nb_ref, nb_img;                 // partial sums per table (spectrum_blocks)
     int16_t *cand;  // [n_ref * n_img][top_k] scratch
     Result *out;
 };

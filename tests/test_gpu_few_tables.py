@@ -119,3 +119,47 @@ def test_references_sharing_a_block(api, oracle, L, n, Q, refs, images, prec):
     g = api.unpack_results(res[torch.tensor(ok, device="cuda")])
     parity.check(g, o, L, parity.TAU_BF16 if prec else parity.TAU_FP32, o["curve"])
     ctx.close()
+
+
+# 2,026 and 2,636: the most tables whose spectra and candidates fit the no-alloc
+# scratch while the norms that prune candidates do not
+@pytest.mark.parametrize("n,count", [(64, 2026), (32, 2636)])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_pruned_candidates_never_win(api, n, count, mode):
+    """All pairs with the candidates that cannot win pruned (the norms fit the
+    call's scratch) against the same pairs with every candidate rescored (the
+    no-alloc scratch has no room for the norms): the same records.  The images
+    hold clean and noisy blobs, noise, nearly symmetric images whose curves are
+    almost flat, copies, an empty image and a NaN."""
+    import torch
+
+    L = n
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5 + n)
+    ax = (torch.arange(L, device="cuda") - (L - 1) / 2) * (2.0 / L)
+    k = 6
+
+    def blobs(m):
+        c = 1.2 * torch.rand(m, k, 2, generator=gen, device="cuda") - 0.6
+        gx = torch.exp(-((ax - c[..., :1]) ** 2) / 0.02)
+        gy = torch.exp(-((ax - c[..., 1:]) ** 2) / 0.02)
+        return torch.bmm(gy.transpose(1, 2).contiguous(), gx.contiguous())
+
+    x = torch.cat([blobs(count // 2), torch.rand(count // 4, L, L, generator=gen, device="cuda")])
+    disc = torch.exp(-(ax[:, None] ** 2 + ax[None, :] ** 2) / 0.1)
+    rest = count - x.shape[0]
+    x = torch.cat([x, disc + 1e-4 * torch.rand(rest, L, L, generator=gen, device="cuda")])
+    x += 0.3 * torch.rand(count, 1, 1, generator=gen, device="cuda") * torch.rand(
+        x.shape, generator=gen, device="cuda") * (torch.arange(count, device="cuda") % 2)[:, None, None]
+    x[7] = 0.0
+    x[11, L // 2, L // 2] = float("nan")
+    x[13] = disc
+    x[17] = x[3]
+    y = x[torch.randperm(count, generator=gen, device="cuda")].contiguous()
+    ctx = api.Context(0)
+    q, a = api.tables(ctx, x.contiguous(), n, n)
+    p, b = api.tables(ctx, y, n, n)
+    pruned, _ = api.align_batch(ctx, q, a, p, b, L, mode=mode, prec=1)
+    every, _ = api.align_batch(ctx, q, a, p, b, L, mode=mode, prec=1, noalloc=True)
+    assert torch.equal(pruned, every)
+    ctx.close()
