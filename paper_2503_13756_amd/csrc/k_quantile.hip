@@ -154,11 +154,7 @@ __global__ __launch_bounds__(NT) void k_quantile_cols(const float *__restrict__ 
         __threadfence();  // the block's sums, before the count
         last = atomicAdd(done + g, 1u) == gridDim.y * parts - 1;
     }
-    float *U = qt + (g * parts + part) * (int64_t)Q * n + k0;
-    for (int idx = threadIdx.x; idx < Q * TC; idx += NT) {
-        const int j = idx / TC, kl = idx - j * TC;
-        U[(int64_t)j * n + kl] = Ut[j * (TC + 1) + kl];
-    }
+    write_tile<NT>(Ut, Q, TC, n, qt + (g * parts + part) * (int64_t)Q * n + k0);
     __syncthreads();
     if (!last || wave != 0 || !aux) return;
     __threadfence();  // every block's sums are visible from here on

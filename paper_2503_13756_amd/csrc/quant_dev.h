@@ -248,21 +248,29 @@ __device__ __forceinline__ void invert_tile(ColFn col, int L, int Q, int levels,
     }
 }
 
+// The tile's rows to the table (row stride n): TC is a power of two up to 64
+// (pick_tc) and divides NT, so a thread keeps its column and steps over rows.
+template <int NT>
+__device__ __forceinline__ void write_tile(const float *Ut, int Q, int TC, int n,
+                                           float *__restrict__ U) {
+    const int lg = 31 - __builtin_clz(TC), kl = threadIdx.x & (TC - 1), dj = NT >> lg;
+    int j = threadIdx.x >> lg;
+    const float *src = Ut + __mul24(j, TC + 1) + kl;
+    float *dst = U + __mul24(j, n) + kl;
+    for (; j < Q; j += dj, src += __mul24(dj, TC + 1), dst += __mul24(dj, n)) *dst = *src;
+}
+
 // All tiles of columns of one image: invert a tile into Ut, then write it
 // out as rows of the [Q][n] table (angle fastest).  Returns the mass of
 // column 0 (on the lanes that inverted it).
 template <int NT, bool HALF, typename ColFn>
 __device__ double quantile_tiles(ColFn col, int L, int n, int Q, int levels, int TC, float *Ut,
                                  double *colS, float *__restrict__ U) {
-    const int ldt = TC + 1;
     double mass0 = 0.0;
     for (int k0 = 0; k0 < n; k0 += TC) {
         invert_tile<NT, HALF>(col, L, Q, levels, TC, k0, Ut, colS, &mass0);
         __syncthreads();
-        for (int idx = threadIdx.x; idx < Q * TC; idx += NT) {
-            const int j = idx / TC, kl = idx - j * TC;
-            U[(int64_t)j * n + k0 + kl] = Ut[j * ldt + kl];
-        }
+        write_tile<NT>(Ut, Q, TC, n, U + k0);
         __syncthreads();
     }
     return mass0;
