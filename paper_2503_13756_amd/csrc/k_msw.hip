@@ -9,12 +9,17 @@
 // are then rescored as direct residual sums (no cancellation), and the
 // smallest rescored value wins (ties to the smaller lag).
 //
-// One 4-wave block per pair, n a multiple of 16 up to 128.  Wave w owns the
-// row blocks a = w, w + 4 (those below n / 16) of the 16 x 16 tiles of C and
-// all column blocks; V streams through LDS in chunks
-// of 64 rows (row stride n + 16 floats, so the four rows of a B fragment fall
-// in distinct banks), U comes straight from global memory (the reference
-// tables are L2-resident).
+// One block per pair, n a multiple of 16 up to 128: W waves own RA row blocks
+// each of the 16 x 16 tiles of C (W RA = n / 16, so that no wave multiplies
+// padding) and all column blocks; V streams through LDS in chunks of 32 rows
+// (row stride n + 16 floats, so the four rows of a B fragment fall in distinct
+// banks), U comes straight from global memory (the reference tables are
+// L2-resident).  The next chunk's rows of both are loaded into registers while
+// the current one is multiplied, and the column energies come out of the same
+// fragments.  The matrix products are 34 us of 3,001 pairs at n = Q = 96; the
+// rest is latency: 238 -> 98 us against four waves with a quarter of
+// their products padding and a serial energy loop on n threads (chunks of 64
+// rows, not prefetched).
 #include "sw_internal.h"
 
 namespace sw {
@@ -22,13 +27,21 @@ namespace sw {
 typedef float f32x4m __attribute__((ext_vector_type(4)));
 
 template <int NN>
-__global__ __launch_bounds__(256) void k_align_msw(PairArgs a, Geo g) {
+struct MswShape {
+    static constexpr int NB = NN / 16, RA = NB > 4 ? 2 : 1, W = NB / RA, NT = 64 * W;
+};
+
+template <int NN>
+__global__ __launch_bounds__(MswShape<NN>::NT) void k_align_msw(PairArgs a, Geo g) {
     static_assert(NN % 16 == 0 && NN <= 128, "n a multiple of 16 up to 128");
-    constexpr int NB = NN / 16, RA = (NB + 3) / 4, KC = 64, VS = NN + 16;
+    constexpr int NB = MswShape<NN>::NB, RA = MswShape<NN>::RA, W = MswShape<NN>::W,
+                  NT = MswShape<NN>::NT;
+    constexpr int KC = 32, KS = KC / 4, VS = NN + 16, VL = KC * (NN / 4) / NT;
+    static_assert(W * RA == NB && VL * NT == KC * (NN / 4), "msw layout");
     __shared__ float vs[KC * VS];
     __shared__ float uu[NN], vv[NN];
     __shared__ unsigned Dbits[NN];
-    __shared__ float colred[256];
+    __shared__ float colred[NT];
     __shared__ int cand[kMaxTopK];
     __shared__ float cval[kMaxTopK];
     const int Q = g.Q;
@@ -56,89 +69,110 @@ __global__ __launch_bounds__(256) void k_align_msw(PairArgs a, Geo g) {
             res->status = status;
         }
         if (curve)
-            for (int l = t; l < NN; l += 256) curve[l] = __int_as_float(0x7fc00000);
+            for (int l = t; l < NN; l += NT) curve[l] = __int_as_float(0x7fc00000);
         return;
     }
     const float *U = a.ref_qt + r * (int64_t)Q * NN;
     const float *V = a.img_qt + gi * (int64_t)Q * NN;
-    for (int i = t; i < NN; i += 256) Dbits[i] = 0u;
-    float uacc = 0.f, vacc = 0.f;  // thread t < NN: column energies of U and V
+    for (int i = t; i < NN; i += NT) Dbits[i] = 0u;
     f32x4m acc[RA][NB];
 #pragma unroll
     for (int ra = 0; ra < RA; ++ra)
 #pragma unroll
         for (int b = 0; b < NB; ++b) acc[ra][b] = f32x4m{0.f, 0.f, 0.f, 0.f};
-    const bool rows_live = wave < NB;  // NN = 64: every wave owns one row block
-    for (int j0 = 0; j0 < Q; j0 += KC) {
-        __syncthreads();
-        for (int q = t; q < KC * (NN / 4); q += 256) {
-            const int jr = q / (NN / 4), c4 = q - jr * (NN / 4);
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (j0 + jr < Q) v = *(const float4 *)(V + (int64_t)(j0 + jr) * NN + 4 * c4);
-            *(float4 *)(vs + jr * VS + 4 * c4) = v;
+    // column energies: U's in this wave's row blocks (lane: column li, rows lk
+    // mod 4), V's in the column blocks b = wave, wave + W, ..
+    float ue[RA], ve[(NB + W - 1) / W];
+#pragma unroll
+    for (int ra = 0; ra < RA; ++ra) ue[ra] = 0.f;
+#pragma unroll
+    for (int i = 0; i < (NB + W - 1) / W; ++i) ve[i] = 0.f;
+    // A fragments A[i][kk] = U[j0 + 4 s + kk][16 (wave + W ra) + i] and the
+    // thread's float4s of V's rows, of the chunk at j0; 0 past row Q
+    float afr[2][RA][KS];
+    float4 vld[VL];
+    auto fetch = [&](int j0, float(&A)[RA][KS]) {
+#pragma unroll
+        for (int i = 0; i < VL; ++i) {
+            const int q = t + NT * i, jr = q / (NN / 4), c4 = q - jr * (NN / 4);
+            vld[i] = j0 + jr < Q ? *(const float4 *)(V + (int64_t)(j0 + jr) * NN + 4 * c4)
+                                 : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int ra = 0; ra < RA; ++ra)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const int j = j0 + 4 * s + lk;
+                A[ra][s] = j < Q ? U[(int64_t)j * NN + 16 * (wave + W * ra) + li] : 0.f;
+            }
+    };
+    fetch(0, afr[0]);
+    auto chunk = [&](int j0, float(&A)[RA][KS], float(&An)[RA][KS]) {
+        __syncthreads();  // the previous chunk is no longer read
+#pragma unroll
+        for (int i = 0; i < VL; ++i) {
+            const int q = t + NT * i, jr = q / (NN / 4), c4 = q - jr * (NN / 4);
+            *(float4 *)(vs + jr * VS + 4 * c4) = vld[i];
         }
         __syncthreads();
-        if (t < NN) {
-            for (int jr = 0; jr < KC && j0 + jr < Q; ++jr) {
-                const float x = vs[jr * VS + t];
-                const float u = U[(int64_t)(j0 + jr) * NN + t];
-                vacc = fmaf(x, x, vacc);
-                uacc = fmaf(u, u, uacc);
-            }
-        }
-        if (rows_live) {
-            // A fragments: A[i][kk] = U[j0 + 4 s + kk][16 a + i]
-            float afr[RA][KC / 4];
+        if (j0 + KC < Q) fetch(j0 + KC, An);
 #pragma unroll
-            for (int ra = 0; ra < RA; ++ra) {
-                const int ab = wave + 4 * ra;
+        for (int ra = 0; ra < RA; ++ra)
 #pragma unroll
-                for (int s = 0; s < KC / 4; ++s) {
-                    const int j = j0 + 4 * s + lk;
-                    afr[ra][s] = j < Q && ab < NB ? U[(int64_t)j * NN + 16 * ab + li] : 0.f;
-                }
-            }
+            for (int s = 0; s < KS; ++s) ue[ra] = fmaf(A[ra][s], A[ra][s], ue[ra]);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            if (j0 + 4 * s >= Q) break;  // uniform: Q is a multiple of 4
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
+                // B[kk][jj] = V[j0 + 4 s + kk][16 b + jj]
+                const float bfr = vs[(4 * s + lk) * VS + 16 * b + li];
+                if (b % W == wave) ve[b / W] = fmaf(bfr, bfr, ve[b / W]);  // wave-uniform
 #pragma unroll
-                for (int s = 0; s < KC / 4; ++s) {
-                    // B[kk][jj] = V[j0 + 4 s + kk][16 b + jj]
-                    const float bfr = vs[(4 * s + lk) * VS + 16 * b + li];
-#pragma unroll
-                    for (int ra = 0; ra < RA; ++ra)
-                        acc[ra][b] =
-                            __builtin_amdgcn_mfma_f32_16x16x4f32(afr[ra][s], bfr, acc[ra][b], 0, 0, 0);
-                }
+                for (int ra = 0; ra < RA; ++ra)
+                    acc[ra][b] =
+                        __builtin_amdgcn_mfma_f32_16x16x4f32(A[ra][s], bfr, acc[ra][b], 0, 0, 0);
             }
         }
+    };
+    for (int j0 = 0; j0 < Q; j0 += 2 * KC) {
+        chunk(j0, afr[0], afr[1]);
+        if (j0 + KC < Q) chunk(j0 + KC, afr[1], afr[0]);
     }
-    if (t < NN) {
-        uu[t] = uacc;
-        vv[t] = vacc;
+    // sum the four row classes of every column
+    auto rows4 = [&](float x) {
+        x += __shfl_xor(x, 16, 64);
+        return x + __shfl_xor(x, 32, 64);
+    };
+#pragma unroll
+    for (int ra = 0; ra < RA; ++ra) {
+        const float x = rows4(ue[ra]);
+        if (lk == 0) uu[16 * (wave + W * ra) + li] = x;
+    }
+#pragma unroll
+    for (int i = 0; i < (NB + W - 1) / W; ++i) {
+        const float x = rows4(ve[i]);
+        if (lk == 0 && wave + W * i < NB) vv[16 * (wave + W * i) + li] = x;
     }
     __syncthreads();
     // residual of column k at lag (k' - k) mod n, max over k by atomics
     const float invQ = 1.f / (float)Q;
-    if (rows_live) {
 #pragma unroll
-        for (int ra = 0; ra < RA; ++ra) {
-            const int ab = wave + 4 * ra;
-            if (ab >= NB) continue;  // wave-uniform
+    for (int ra = 0; ra < RA; ++ra) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
+        for (int b = 0; b < NB; ++b) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int k = 16 * ab + 4 * lk + e, kp = 16 * b + li;
-                    const float v = fmaxf((uu[k] + vv[kp] - 2.f * acc[ra][b][e]) * invQ, 0.f);
-                    const int lag = kp >= k ? kp - k : kp - k + NN;
-                    atomicMax(&Dbits[lag], __float_as_uint(v));
-                }
+            for (int e = 0; e < 4; ++e) {
+                const int k = 16 * (wave + W * ra) + 4 * lk + e, kp = 16 * b + li;
+                const float v = fmaxf((uu[k] + vv[kp] - 2.f * acc[ra][b][e]) * invQ, 0.f);
+                const int lag = kp >= k ? kp - k : kp - k + NN;
+                atomicMax(&Dbits[lag], __float_as_uint(v));
             }
         }
     }
     __syncthreads();
     if (curve)
-        for (int l = t; l < NN; l += 256) curve[l] = __uint_as_float(Dbits[l]);
+        for (int l = t; l < NN; l += NT) curve[l] = __uint_as_float(Dbits[l]);
     // top_k lags of the estimate (wave 0; ties to the smaller lag)
     const int K = a.top_k;
     if (wave == 0) {
@@ -168,16 +202,23 @@ __global__ __launch_bounds__(256) void k_align_msw(PairArgs a, Geo g) {
     __syncthreads();
     // rescore: direct FP32 column residuals at every candidate, max over k
     // (threads past TPC n idle)
-    constexpr int TPC = 256 / NN;  // threads per column
+    constexpr int TPC = NT / NN;  // threads per column
     const int k = t % NN, part = t / NN;
     for (int c = 0; c < K; ++c) {
         const int l = cand[c];
         const float *Vc = V + (k + l < NN ? k + l : k + l - NN);
         float s = 0.f;
         if (part < TPC)
-            for (int j = part; j < Q; j += TPC) {
-                const float d = U[(int64_t)j * NN + k] - Vc[(int64_t)j * NN];
-                s = fmaf(d, d, s);
+            for (int j0 = part; j0 < Q; j0 += 8 * TPC) {  // eight rows' loads in flight
+                float d[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int64_t o = (int64_t)min(j0 + i * TPC, Q - 1) * NN;
+                    d[i] = U[o + k] - Vc[o];
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (j0 + i * TPC < Q) s = fmaf(d[i], d[i], s);
             }
         colred[t] = s;
         __syncthreads();
@@ -215,7 +256,7 @@ bool msw_supported(Geo g) { return g.n % 16 == 0 && g.n <= 128; }
 
 template <int NN>
 static void launch_msw_t(const PairArgs &a, Geo g, int64_t P, hipStream_t s) {
-    hipLaunchKernelGGL((k_align_msw<NN>), dim3((unsigned)P), dim3(256), 0, s, a, g);
+    hipLaunchKernelGGL((k_align_msw<NN>), dim3((unsigned)P), dim3(MswShape<NN>::NT), 0, s, a, g);
 }
 
 hipError_t launch_align_msw(const PairArgs &a, Geo g, hipStream_t s) {
