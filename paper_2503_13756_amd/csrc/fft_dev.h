@@ -44,12 +44,12 @@ __device__ __forceinline__ int div_small(int x, float inv) {
 }
 
 // One Stockham pass of radix R over `rows` complex rows of length n, from X
-// to Y (row stride n).  p = product of the radices already applied.  The
+// to Y (row stride rs).  p = product of the radices already applied.  The
 // indices are quotients by n / R and by p, which integer division would make
 // most of the pass's instructions.
 template <int NT, int R>
-__device__ __forceinline__ void fft_pass(const float2 *X, float2 *Y, int rows, int n, int p,
-                                         const float2 *tw) {
+__device__ __forceinline__ void fft_pass(const float2 *X, float2 *Y, int rows, int n, int rs,
+                                         int p, const float2 *tw) {
     const int nr = n / R;
     const int nb = rows * nr;
     const int ts = n / (p * R);
@@ -57,7 +57,7 @@ __device__ __forceinline__ void fft_pass(const float2 *X, float2 *Y, int rows, i
     for (int idx = threadIdx.x; idx < nb; idx += NT) {
         const int row = div_small(idx, inr), i = idx - __mul24(row, nr);
         const int k = i - __mul24(div_small(i, ip), p);
-        const float2 *x = X + __mul24(row, n) + i;
+        const float2 *x = X + __mul24(row, rs) + i;
         float2 v[R];
         int m = 0;  // q k ts
         const int dm = __mul24(k, ts);
@@ -68,35 +68,51 @@ __device__ __forceinline__ void fft_pass(const float2 *X, float2 *Y, int rows, i
             m += dm;
         }
         dft_small<R>(v);
-        float2 *y = Y + __mul24(row, n) + __mul24(i - k, R) + k;
+        float2 *y = Y + __mul24(row, rs) + __mul24(i - k, R) + k;
 #pragma unroll
         for (int q = 0; q < R; ++q) y[q * p] = v[q];
     }
     __syncthreads();
 }
 
-// Forward FFT of `rows` rows held in A; B is a buffer of the same size.
-// Returns the buffer holding the result.
+// Forward FFT of `rows` rows (row stride rs) held in A; B is a buffer of the
+// same size.  The radices of product p have been applied already.  Returns the
+// buffer holding the result.
 template <int NT>
-__device__ float2 *fft_rows(float2 *A, float2 *B, int rows, int n, const float2 *tw) {
-    int p = 1, m = n;
+__device__ float2 *fft_rows(float2 *A, float2 *B, int rows, int n, int rs, int p,
+                            const float2 *tw) {
+    int m = n / p;
     float2 *x = A, *y = B;
     while (m % 4 == 0) {
-        fft_pass<NT, 4>(x, y, rows, n, p, tw);
+        fft_pass<NT, 4>(x, y, rows, n, rs, p, tw);
         p *= 4; m /= 4;
         float2 *t = x; x = y; y = t;
     }
     while (m % 3 == 0) {
-        fft_pass<NT, 3>(x, y, rows, n, p, tw);
+        fft_pass<NT, 3>(x, y, rows, n, rs, p, tw);
         p *= 3; m /= 3;
         float2 *t = x; x = y; y = t;
     }
     while (m % 2 == 0) {
-        fft_pass<NT, 2>(x, y, rows, n, p, tw);
+        fft_pass<NT, 2>(x, y, rows, n, rs, p, tw);
         p *= 2; m /= 2;
         float2 *t = x; x = y; y = t;
     }
     return x;
+}
+template <int NT>
+__device__ float2 *fft_rows(float2 *A, float2 *B, int rows, int n, const float2 *tw) {
+    return fft_rows<NT>(A, B, rows, n, n, 1, tw);
+}
+
+// Passes that fft_rows takes for length n, the radices of product p left out
+// (n / p here).
+__host__ __device__ inline int fft_passes(int n) {
+    int c = 0;
+    for (; n % 4 == 0; n /= 4) ++c;
+    for (; n % 3 == 0; n /= 3) ++c;
+    for (; n % 2 == 0; n /= 2) ++c;
+    return c;
 }
 
 }  // namespace sw

@@ -556,16 +556,27 @@ static double es_phi(double z) {
 // directions d = (c[m], -s[m]): for each slice m and k = 0 .. L/2, the
 // fine-grid point g = k d Nf / L of the slice frequency k pi d (mirrored to
 // g_x >= 0, the conjugate then taken in the kernel), its first tap row u0
-// and column v0 of the kernel's support, the kernel weights per row and
-// column, and the factor exp(-i pi k (d_x + d_y) / L) sinc(pi k d_x / L)
+// and the ring slot of its first column v0, the kernel weights per row and
+// column, the factor exp(-i pi k (d_x + d_y) / L) sinc(pi k d_x / L)
 // sinc(pi k d_y / L) (the pixel centres' half-pixel offset and the transform
-// of one pixel cell), all from FP64.  Layout as read by slice_point in
-// k_fourier.hip.
+// of one pixel cell), and the point's index m (L/2 + 1) + k, all from FP64.
+// Layout as read by slice_points in k_fourier.hip, the steps' first points (as
+// ints) behind it.
+//
+// The points are ordered by the round of columns that completes their support
+// (the last columns to come are v0 + 6), and those of a round so that the lanes
+// of a wave start in different LDS banks: a first element's bank pair is its
+// offset mod 32, and the points are dealt from the 32 classes in turn.
 static std::vector<float4> fourier_target_table(int L, const std::vector<double> &c,
                                                 const std::vector<double> &s) {
     const double pi = 3.141592653589793238462643383279502884;
     const int M = L / 2, Nf = 2 * L, W = sw::kFourierW, nsl = (int)c.size();
-    std::vector<float4> tab((size_t)nsl * (M + 1) * 5);
+    const int G = sw::fourier_group(L), RC = 2 * G, CS = sw::fourier_stride(Nf);
+    const int rounds = sw::fourier_rounds(L), npts = nsl * (M + 1);
+    struct Point {
+        float4 e[5];
+    };
+    std::vector<std::vector<Point>> bins((size_t)(rounds + 1) * 32);  // [round][bank pair]
     for (int m = 0; m < nsl; ++m) {
         const double dx = c[m], dy = -s[m];
         const bool flip = dx < 0.0;
@@ -580,17 +591,36 @@ static std::vector<float4> fourier_target_table(int L, const std::vector<double>
             }
             const double ax = pi * k * dx / L, ay = pi * k * dy / L, ang = -(ax + ay);
             const double sinc = (ax == 0.0 ? 1.0 : std::sin(ax) / ax) * (ay == 0.0 ? 1.0 : std::sin(ay) / ay);
-            float4 *e = &tab[((size_t)m * (M + 1) + k) * 5];
-            int hdr[2] = {((u0 % Nf) + Nf) % Nf, (v0 + sw::kFourierPad) | (flip ? 1 << 16 : 0)};
-            float hf[2];
+            // 0 <= g_x <= L: v0 >= -3 and v0 + 6 <= L + 3
+            const int row = ((u0 % Nf) + Nf) % Nf, slot = (v0 + sw::fourier_first(L)) & (RC - 1);
+            const int last = v0 + W - 1;
+            const int round = last < L ? last / G : sw::fourier_tail(L) ? rounds : rounds - 1;
+            const int hdr[3] = {row, slot | (flip ? 1 << 16 : 0), m * (M + 1) + k};
+            float hf[3];
             std::memcpy(hf, hdr, sizeof(hf));
-            e[0] = make_float4(hf[0], hf[1], (float)(std::cos(ang) * sinc), (float)(std::sin(ang) * sinc));
-            e[1] = make_float4(wx[0], wx[1], wx[2], wx[3]);
-            e[2] = make_float4(wx[4], wx[5], wx[6], 0.f);
-            e[3] = make_float4(wy[0], wy[1], wy[2], wy[3]);
-            e[4] = make_float4(wy[4], wy[5], wy[6], 0.f);
+            bins[(size_t)round * 32 + (slot * CS + row) % 32].push_back(
+                {{make_float4(hf[0], hf[1], (float)(std::cos(ang) * sinc), (float)(std::sin(ang) * sinc)),
+                  make_float4(wx[0], wx[1], wx[2], wx[3]), make_float4(wx[4], wx[5], wx[6], hf[2]),
+                  make_float4(wy[0], wy[1], wy[2], wy[3]), make_float4(wy[4], wy[5], wy[6], 0.f)}});
         }
     }
+    std::vector<float4> tab((size_t)npts * 5);
+    std::vector<int> steps(rounds + 2, 0);
+    int i = 0;
+    for (int r = 0; r <= rounds; ++r) {
+        size_t most = 0;
+        for (int b = 0; b < 32; ++b) most = std::max(most, bins[(size_t)r * 32 + b].size());
+        for (size_t d = 0; d < most; ++d)
+            for (int b = 0; b < 32; ++b) {
+                const std::vector<Point> &v = bins[(size_t)r * 32 + b];
+                if (d >= v.size()) continue;
+                for (int q = 0; q < 5; ++q) tab[(size_t)q * npts + i] = v[d].e[q];
+                ++i;
+            }
+        steps[r + 1] = i;
+    }
+    tab.resize((size_t)npts * 5 + (steps.size() + 3) / 4);
+    std::memcpy(&tab[(size_t)npts * 5], steps.data(), sizeof(int) * steps.size());
     return tab;
 }
 
@@ -1168,7 +1198,6 @@ static sw_status fourier_setup(Ctx *c, const sw::Geo &geo, int64_t N, const doub
     S->Nf = 2 * geo.L;
     S->lgNf = lg < 0 ? -1 : lg + 1;
     S->lgL = lg;
-    S->H = geo.L + 1;
     S->mirror = theta ? 0 : 1;
     sw_status st = get_fourier_tabs(c, geo.L, T);
     if (st != SW_OK) return st;
@@ -1182,12 +1211,21 @@ static sw_status fourier_setup(Ctx *c, const sw::Geo &geo, int64_t N, const doub
         if (st == SW_OK) st = get_table(c, geo.n, dirs);
     }
     if (st != SW_OK) return st;
-    // one slot per block that can be resident at once, at most two per CU (a
-    // third block at L = 128 fits but costs 4 % through its scratch traffic)
-    const int64_t cap =
-        (int64_t)std::min(sw::fourier_blocks_per_cu(S->L, S->Nf), 2) * c->cu_count;
+    T->steps = (const int *)(T->targets + 5 * (size_t)sw::fourier_slices(*S) * (geo.L / 2 + 1));
+    // one slot per block that can be resident at once
+    const int64_t cap = (int64_t)sw::fourier_blocks_per_cu(*S) * c->cu_count;
     *slots = (int)(N < cap ? N : cap);
     return SW_OK;
+}
+
+// Images whose phases are spread over blocks, one launch each, rather than one
+// block per image: one image takes 28 us instead of 79 at L = 128, 40 instead
+// of 246 at 256 (nothing is gained up to L = 64, 26 us both ways).  A round's
+// block repeats the column transforms of the round before, so that full
+// devices lose: the lines cross between 0.37 (L = 192) and 0.65 (L = 128)
+// images per compute unit.
+static bool fourier_few(const Ctx *c, const sw::Geo &geo, int64_t N) {
+    return geo.L > 64 && (c->small_batch >= 0 ? c->small(N) : 3 * N <= c->cu_count);
 }
 
 static sw_status project_fourier(void *ctx, const float *img, int64_t N, const sw_geom *g,
@@ -1210,9 +1248,9 @@ static sw_status project_fourier(void *ctx, const float *img, int64_t N, const s
     (void)dirs;  // the projection needs the slice-point table only
     hipStream_t s = (hipStream_t)stream;
     void *scr;
-    if ((st = get_scratch(c, sw::fourier_slot_bytes(S.L, S.Nf) * slots, s, &scr)) != SW_OK)
+    if ((st = get_scratch(c, sw::fourier_slot_bytes(S) * slots, s, &scr)) != SW_OK)
         return st;
-    hipError_t e = sw::launch_fourier(img, N, S, T, scr, slots, pmf, s);
+    hipError_t e = sw::launch_fourier(img, N, S, T, scr, slots, fourier_few(c, geo, N), pmf, s);
     return e == hipSuccess ? SW_OK : hip_fail(e, "k_fourier launch");
 }
 
@@ -1253,7 +1291,7 @@ static sw_status tables_fourier(void *ctx, const float *img, int64_t N, const sw
     if (chunk > N) chunk = N;
     const size_t pmf_bytes = (per * (size_t)chunk + 255) & ~(size_t)255;
     const size_t slot_bytes =
-        (sw::fourier_slot_bytes(S.L, S.Nf) * slots + 255) & ~(size_t)255;
+        (sw::fourier_slot_bytes(S) * slots + 255) & ~(size_t)255;
     // after the slots, the column sums of the largest chunk that is a small batch
     const int64_t few = c->small(chunk) ? chunk : c->small(N % chunk) ? N % chunk : 0;
     const size_t cols_bytes = sw::quantile_cols_bytes(few, geo.n, 1);
@@ -1265,7 +1303,7 @@ static sw_status tables_fourier(void *ctx, const float *img, int64_t N, const sw
     for (int64_t i0 = 0; i0 < N; i0 += chunk) {
         const int64_t m = N - i0 < chunk ? N - i0 : chunk;
         hipError_t e = sw::launch_fourier(img + i0 * (int64_t)geo.L * geo.L, m, S, T, slot_mem,
-                                          slots, pmf, s,
+                                          slots, fourier_few(c, geo, m), pmf, s,
                                           c->small(m) ? sw::quantile_cols_done(cols) : nullptr);
         if (e != hipSuccess) return hip_fail(e, "k_fourier launch");
         e = sw::launch_quantiles(pmf, m, geo, *dirs, qt + i0 * (int64_t)geo.Q * geo.n,

@@ -163,3 +163,34 @@ def test_pruned_candidates_never_win(api, n, count, mode):
     every, _ = api.align_batch(ctx, q, a, p, b, L, mode=mode, prec=1, noalloc=True)
     assert torch.equal(pruned, every)
     ctx.close()
+
+
+# Fourier slices: a single round of columns with its slot in LDS (L <= 36; the
+# slot in scratch at n = 512), several rounds with the last one short or taking
+# column L along (L <= 64), a step of its own for column L; explicit angles
+@pytest.mark.parametrize("L,n", [(8, 8), (12, 16), (16, 512), (32, 32), (36, 512), (36, 32),
+                                 (48, 24), (54, 48), (72, 72), (108, 64), (128, 24), (162, 48),
+                                 (256, 128)])
+@pytest.mark.parametrize("theta", [False, True])
+def test_fourier_rounds(api, oracle, tmp_path, L, n, theta):
+    """The phases of an image over several blocks against one block per image
+    bit for bit, and both against the oracle at the projector's tolerance
+    (5e-6 of the largest value), with a NaN image among them."""
+    _, imgs = synth.make_raw_stack(55 + L, L, 4)
+    ang = synth.mc_angles(n, 3) if theta else None
+    imgs[2, L // 2, L // 2] = np.nan
+    x = dev(imgs)
+    out = {}
+    for name, lim in (("split", 1 << 30), ("whole", 0)):
+        path = tmp_path / f"{name}.json"
+        path.write_text('{"small_batch": %d}' % lim)
+        ctx = api.Context(0, str(path))
+        out[name] = api.project_fourier(ctx, x, n, theta=ang).cpu().numpy()
+        ctx.close()
+    assert np.array_equal(out["split"], out["whole"], equal_nan=True)
+    got = out["split"]
+    assert np.isnan(got[2]).all()
+    keep = [0, 1, 3]
+    P0 = np.maximum(oracle.fourier_project(imgs[keep], n, angles=ang)[0], 0.0)
+    err = np.abs(got[keep] - P0).max(axis=(1, 2)) / P0.max(axis=(1, 2))
+    assert err.max() < 5e-6, err
