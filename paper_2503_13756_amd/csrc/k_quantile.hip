@@ -27,63 +27,22 @@ __global__ __launch_bounds__(NT) void k_quantile(const float *__restrict__ pmf, 
 // Sec. 2.3 and its appendix).  aux = { smallest part mass over the columns
 // (NaN if a value is NaN), E of the stacked table, a of the stacked table =
 // the mean of the two parts' moments }.
-template <int NT>
+template <int NT, int QM>
 __global__ __launch_bounds__(NT) void k_quantile_rf(const float *__restrict__ pf, int64_t N,
                                                     QuantShape<NT> S,
                                                     const double2 *__restrict__ d64,
                                                     float *__restrict__ qt,
                                                     double *__restrict__ aux) {
-    constexpr int NW = NT / 64;
     extern __shared__ __align__(16) double ldsd[];
-    __shared__ double partA[2][4];
-    __shared__ double wmin[NW];
-    __shared__ int wnan[NW];
     const int64_t g = blockIdx.x;
     if (g >= N) return;
     const int L = S.L, n = S.n, Q = S.Q;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double *colS = ldsd;
     float *Ut = (float *)(colS + 2 * n);
     const float *P = pf + g * (int64_t)n * L;
-    float *U = qt + g * (int64_t)2 * Q * n;
-    quantile_phase<NT>([&](int k, int b) { return fmaxf(P[(int64_t)k * L + b], 0.f); }, L, n, Q,
-                       S.levels, S.TC, d64, Ut, colS, U, partA[0]);
-    quantile_phase<NT>([&](int k, int b) { return fmaxf(-P[(int64_t)k * L + b], 0.f); }, L, n,
-                       Q, S.levels, S.TC, d64, Ut, colS, U + (int64_t)Q * n, partA[1]);
-    // smallest part mass over the columns, for the status of the image
-    double mn = INFINITY;
-    int bad = 0;
-    for (int k = wave; k < n; k += NW) {
-        double sp = 0.0, sm = 0.0;
-        for (int b = lane; b < L; b += 64) {
-            const float v = P[(int64_t)k * L + b];
-            if (v != v) bad = 1;
-            sp += (double)fmaxf(v, 0.f);
-            sm += (double)fmaxf(-v, 0.f);
-        }
-        sp = wave_sum_d(sp);
-        sm = wave_sum_d(sm);
-        mn = fmin(mn, fmin(sp, sm));
-    }
-    bad = __any(bad);
-    if (lane == 0) {
-        wmin[wave] = mn;
-        wnan[wave] = bad;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && aux) {
-        double m = wmin[0];
-        int nb = wnan[0];
-        for (int w = 1; w < NW; ++w) {
-            m = fmin(m, wmin[w]);
-            nb |= wnan[w];
-        }
-        double *A = aux + 4 * g;
-        A[0] = nb ? __longlong_as_double(0x7ff8000000000000LL) : m;
-        A[1] = partA[0][1] + partA[1][1];
-        A[2] = 0.5 * (partA[0][2] + partA[1][2]);
-        A[3] = 0.5 * (partA[0][3] + partA[1][3]);
-    }
+    quantile_phase_rf<NT, QM>([&](int k, int b) { return P[(int64_t)k * L + b]; }, L, n, Q, S.levels,
+                          S.TC, d64, Ut, colS, qt + g * (int64_t)2 * Q * n,
+                          aux ? aux + 4 * g : nullptr);
 }
 
 // Small batches: a block per (image, eight columns[, signed part]) instead of
@@ -107,48 +66,36 @@ __global__ __launch_bounds__(NT) void k_quantile_cols(const float *__restrict__ 
                                                       float *__restrict__ qt,
                                                       double *__restrict__ aux, double *colS,
                                                       double *colM, unsigned *done) {
-    constexpr int NW = NT / 64, TC = kColsPerBlock;
+    constexpr int TC = kColsPerBlock;
     extern __shared__ __align__(16) float Ut[];  // [Q][TC + 1]
-    __shared__ double cs[2 * TC];
-    __shared__ int last;
+    __shared__ double cs[2 * TC], cm[TC];
+    __shared__ int last, nan;
     const int64_t g = blockIdx.x;
     const int k0 = TC * (int)blockIdx.y, part = RF ? (int)blockIdx.z : 0;
     constexpr int parts = RF ? 2 : 1;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float sign = part ? -1.f : 1.f;
     const float *P = pmf + g * (int64_t)n * L;
+    if (RF) {
+        if (threadIdx.x == 0) nan = 0;
+        __syncthreads();
+    }
     auto col = [&](int k, int b) {
         const float v = P[(int64_t)k * L + b];
+        if (RF && v != v) nan = 1;  // every such lane writes the same
         return RF ? fmaxf(sign * v, 0.f) : v;
     };
-    double mass0 = 0.0;
+    auto on_mass = [&](int k, double m) { cm[k - k0] = m; };  // the same on its lanes
     // cs holds the columns k0 .. k0 + TC - 1 of quantile_phase's colS
-    if (L <= 128) invert_tile<NT, true>(col, L, Q, levels, TC, k0, Ut, cs - 2 * k0, &mass0);
-    else invert_tile<NT, false>(col, L, Q, levels, TC, k0, Ut, cs - 2 * k0, &mass0);
+    if (L <= 128) invert_tile<NT, true>(col, L, Q, levels, TC, k0, Ut, cs - 2 * k0, on_mass);
+    else invert_tile<NT, false>(col, L, Q, levels, TC, k0, Ut, cs - 2 * k0, on_mass);
     __syncthreads();
     if (threadIdx.x < 2 * TC)
         colS[((g * parts + part) * n + k0) * 2 + threadIdx.x] = cs[threadIdx.x];
-    if (!RF) {
-        if (k0 == 0 && threadIdx.x == 0) colM[g * n] = mass0;  // column 0 is inverted by wave 0
-    } else if (part == 0) {
-        // the smaller part mass of each column, NaN for a NaN value
-        for (int kl = wave; kl < TC; kl += NW) {
-            double sp = 0.0, sm = 0.0;
-            int bad = 0;
-            for (int b = lane; b < L; b += 64) {
-                const float v = P[(int64_t)(k0 + kl) * L + b];
-                if (v != v) bad = 1;
-                sp += (double)fmaxf(v, 0.f);
-                sm += (double)fmaxf(-v, 0.f);
-            }
-            sp = wave_sum_d(sp);
-            sm = wave_sum_d(sm);
-            bad = __any(bad);
-            if (lane == 0)
-                colM[g * n + k0 + kl] =
-                    bad ? __longlong_as_double(0x7ff8000000000000LL) : fmin(sp, sm);
-        }
-    }
+    // the masses of the columns (or of the parts), NaN for a NaN value
+    if (threadIdx.x < TC)
+        colM[(g * parts + part) * n + k0 + threadIdx.x] =
+            RF && nan ? __longlong_as_double(0x7ff8000000000000LL) : cm[threadIdx.x];
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();  // the block's sums, before the count
@@ -174,8 +121,8 @@ __global__ __launch_bounds__(NT) void k_quantile_cols(const float *__restrict__ 
     }
     double mn = INFINITY;
     int bad = 0;
-    for (int k = lane; k < n; k += 64) {
-        const double m = colM[g * n + k];
+    for (int k = lane; k < 2 * n; k += 64) {
+        const double m = colM[g * 2 * n + k];
         if (m != m) bad = 1;
         else mn = fmin(mn, m);
     }
@@ -191,7 +138,7 @@ __global__ __launch_bounds__(NT) void k_quantile_cols(const float *__restrict__ 
 }
 
 size_t quantile_cols_bytes(int64_t N, int n, int parts) {
-    return sizeof(double) * (size_t)N * (n * (2 * parts + 1) + 1);
+    return sizeof(double) * (size_t)N * (n * 3 * parts + 1);
 }
 
 unsigned *quantile_cols_done(void *cols) { return (unsigned *)cols; }
@@ -238,16 +185,17 @@ hipError_t launch_quantiles(const float *pmf, int64_t N, Geo g, const AngleTable
 }
 
 
-template <int NT>
+template <int NT, int QM>
 static hipError_t launch_quantiles_rf_t(const float *pf, int64_t N, Geo g, const AngleTable &t,
                                         float *qt, double *aux, hipStream_t s) {
     QuantShape<NT> S{g.L, g.n, g.Q, g.levels, pick_tc(g.n, g.Q, 68 * 1024)};
     const size_t lds = sizeof(double) * 2 * g.n + sizeof(float) * g.Q * (S.TC + 1);
-    static const hipError_t attr = hipFuncSetAttribute(
-        (const void *)k_quantile_rf<NT>, hipFuncAttributeMaxDynamicSharedMemorySize, 120 * 1024);
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_quantile_rf<NT, QM>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                       120 * 1024);
     (void)attr;
-    hipLaunchKernelGGL((k_quantile_rf<NT>), dim3((unsigned)N), dim3(NT), lds, s, pf, N, S, t.d64,
-                       qt, aux);
+    hipLaunchKernelGGL((k_quantile_rf<NT, QM>), dim3((unsigned)N), dim3(NT), lds, s, pf, N, S,
+                       t.d64, qt, aux);
     return hipGetLastError();
 }
 
@@ -255,8 +203,12 @@ hipError_t launch_quantiles_rf(const float *pf, int64_t N, Geo g, const AngleTab
                                double *aux, hipStream_t s, bool small, double *cols) {
     if (N <= 0) return hipSuccess;
     if (small && cols) return launch_quantile_cols<true>(pf, N, g, t, qt, aux, cols, s);
-    if (small) return launch_quantiles_rf_t<1024>(pf, N, g, t, qt, aux, s);
-    return launch_quantiles_rf_t<256>(pf, N, g, t, qt, aux, s);
+    const bool half = quant_mode_for(g.L) == kQuantHalf;
+    if (small)
+        return half ? launch_quantiles_rf_t<1024, kQuantHalf>(pf, N, g, t, qt, aux, s)
+                    : launch_quantiles_rf_t<1024, kQuantWave>(pf, N, g, t, qt, aux, s);
+    return half ? launch_quantiles_rf_t<256, kQuantHalf>(pf, N, g, t, qt, aux, s)
+                : launch_quantiles_rf_t<256, kQuantWave>(pf, N, g, t, qt, aux, s);
 }
 
 }  // namespace sw

@@ -123,12 +123,10 @@ __device__ void rf_image_tail(const TablesShape &T, float *region, const float *
                               const double2 *__restrict__ d64, float *Ut, double *colS, float *U,
                               double *A) {
     constexpr int NW = NT / 64;
-    __shared__ double partA[2][4];
-    __shared__ double wmin[NW];
-    __shared__ int wnan[NW];
     const ProjShape &P = T.P;
     const int L = P.L, n = P.n, Q = T.Q, ldp = L + 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    static_assert(4 * NS <= 128, "columns of at most 128 bins");
+    const int wave = threadIdx.x >> 6;
     for (int tile = wave; tile < (n + 15) / 16; tile += NW) {
         const int c0 = 16 * tile;
         ramp_tile<NS>(
@@ -138,43 +136,9 @@ __device__ void rf_image_tail(const TablesShape &T, float *region, const float *
             });
     }
     __syncthreads();
-    quantile_phase<NT>([&](int k, int b) { return fmaxf(region[k * ldp + b], 0.f); }, L, n, Q,
-                       T.levels, T.TC, d64, Ut, colS, U, partA[0]);
-    quantile_phase<NT>([&](int k, int b) { return fmaxf(-region[k * ldp + b], 0.f); }, L, n, Q,
-                       T.levels, T.TC, d64, Ut, colS, U + (int64_t)Q * n, partA[1]);
-    // smallest part mass over the columns, for the status of the image
-    double mn = INFINITY;
-    int nan = 0;
-    for (int k = wave; k < n; k += NW) {
-        double sp = 0.0, sm = 0.0;
-        for (int b = lane; b < L; b += 64) {
-            const float v = region[k * ldp + b];
-            if (v != v) nan = 1;
-            sp += (double)fmaxf(v, 0.f);
-            sm += (double)fmaxf(-v, 0.f);
-        }
-        sp = wave_sum_d(sp);
-        sm = wave_sum_d(sm);
-        mn = fmin(mn, fmin(sp, sm));
-    }
-    nan = __any(nan);
-    if (lane == 0) {
-        wmin[wave] = mn;
-        wnan[wave] = nan;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && A) {
-        double m = wmin[0];
-        int nb = wnan[0];
-        for (int w = 1; w < NW; ++w) {
-            m = fmin(m, wmin[w]);
-            nb |= wnan[w];
-        }
-        A[0] = nb ? __longlong_as_double(0x7ff8000000000000LL) : m;
-        A[1] = partA[0][1] + partA[1][1];
-        A[2] = 0.5 * (partA[0][2] + partA[1][2]);
-        A[3] = 0.5 * (partA[0][3] + partA[1][3]);
-    }
+    // LP <= 128: columns by half waves
+    quantile_phase_rf<NT, kQuantHalf>([&](int k, int b) { return region[k * ldp + b]; }, L, n, Q,
+                                      T.levels, T.TC, d64, Ut, colS, U, A);
 }
 
 // Fused ramp-filtered tables (ramp-filtered SW of Sec. 2.3): the projection
@@ -220,6 +184,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kProjMinWave
 // 2Qn floats, during the first image's tail), then image by image written
 // into the region with the padded column stride, filtered and inverted.
 // Bitwise the results of k_tables_rf.
+//
+// 4,000 images at L = n = Q = 128: 1,160 -> 1,010 us with the filter's products at
+// the odd offsets only, the parts' masses taken from the inversions instead of
+// a pass of their own, and one body of code for both parts (2 spilled registers
+// instead of 28); the plain tables take 708.
 template <int NT, int TPW, int NS>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tables2_rf(
     const float *__restrict__ img, int64_t N, TablesShape T, const float2 *__restrict__ d32,

@@ -225,10 +225,11 @@ __device__ __forceinline__ double invert_column(ColFn col, int L, int Q, int lev
 }
 
 // Invert the TC columns k0 .. k0 + TC - 1 of a tile: with halves, columns
-// 2 p and 2 p + 1 go to the two halves of wave p (TC is even).
-template <int NT, bool HALF, typename ColFn>
+// 2 p and 2 p + 1 go to the two halves of wave p (TC is even).  mass(k, m)
+// gets every column's mass, on the lanes that inverted it.
+template <int NT, bool HALF, typename ColFn, typename MassFn>
 __device__ __forceinline__ void invert_tile(ColFn col, int L, int Q, int levels, int TC, int k0,
-                                            float *Ut, double *colS, double *mass0) {
+                                            float *Ut, double *colS, MassFn on_mass) {
     constexpr int NW = NT / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int hl = HALF ? lane & 31 : lane, half = HALF ? lane >> 5 : 0;
@@ -238,7 +239,7 @@ __device__ __forceinline__ void invert_tile(ColFn col, int L, int Q, int levels,
         double su, sq;
         const double mass = invert_column<HALF>([&](int b) { return col(k, b); }, L, Q, levels,
                                                 Ut, TC + 1, kl, hl, half, &su, &sq);
-        if (k == 0) *mass0 = mass;
+        on_mass(k, mass);
         su = group_sum_d<HALF>(su, half);
         sq = group_sum_d<HALF>(sq, half);
         if (hl == 0) {
@@ -261,19 +262,16 @@ __device__ __forceinline__ void write_tile(const float *Ut, int Q, int TC, int n
 }
 
 // All tiles of columns of one image: invert a tile into Ut, then write it
-// out as rows of the [Q][n] table (angle fastest).  Returns the mass of
-// column 0 (on the lanes that inverted it).
-template <int NT, bool HALF, typename ColFn>
-__device__ double quantile_tiles(ColFn col, int L, int n, int Q, int levels, int TC, float *Ut,
-                                 double *colS, float *__restrict__ U) {
-    double mass0 = 0.0;
+// out as rows of the [Q][n] table (angle fastest).
+template <int NT, bool HALF, typename ColFn, typename MassFn>
+__device__ void quantile_tiles(ColFn col, int L, int n, int Q, int levels, int TC, float *Ut,
+                               double *colS, float *__restrict__ U, MassFn on_mass) {
     for (int k0 = 0; k0 < n; k0 += TC) {
-        invert_tile<NT, HALF>(col, L, Q, levels, TC, k0, Ut, colS, &mass0);
+        invert_tile<NT, HALF>(col, L, Q, levels, TC, k0, Ut, colS, on_mass);
         __syncthreads();
         write_tile<NT>(Ut, Q, TC, n, U + k0);
         __syncthreads();
     }
-    return mass0;
 }
 
 // Which column inversion a kernel compiles: both, chosen by L at run time,
@@ -315,11 +313,14 @@ __device__ void quantile_phase(ColFn col, int L, int n, int Q, int levels, int T
                                const double2 *__restrict__ d64, float *Ut, double *colS,
                                float *__restrict__ U, double *__restrict__ A) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double mass0;
+    double mass0 = 0.0;
+    auto first = [&](int k, double m) {
+        if (k == 0) mass0 = m;
+    };
     if (QM == kQuantHalf || (QM == kQuantAuto && L <= 128))
-        mass0 = quantile_tiles<NT, true>(col, L, n, Q, levels, TC, Ut, colS, U);
+        quantile_tiles<NT, true>(col, L, n, Q, levels, TC, Ut, colS, U, first);
     else
-        mass0 = quantile_tiles<NT, false>(col, L, n, Q, levels, TC, Ut, colS, U);
+        quantile_tiles<NT, false>(col, L, n, Q, levels, TC, Ut, colS, U, first);
     if (wave == 0) {
         double s[3];
         column_aux(colS, n, Q, d64, lane, s);
@@ -331,6 +332,64 @@ __device__ void quantile_phase(ColFn col, int L, int n, int Q, int levels, int T
         }
     }
     __syncthreads();
+}
+
+// The same for signed (ramp-filtered) columns: their positive parts to rows
+// 0 .. Q - 1 of the stacked table U, their negative parts to rows Q .. 2 Q - 1,
+// and A (nullable) = { smallest part mass (NaN for a NaN value), E and a of the
+// stacked table }.  The masses are those the inversions need anyway; one body
+// of code takes both parts.
+template <int NT, int QM = kQuantAuto, typename ColFn>
+__device__ void quantile_phase_rf(ColFn col, int L, int n, int Q, int levels, int TC,
+                                  const double2 *__restrict__ d64, float *Ut, double *colS,
+                                  float *__restrict__ U, double *__restrict__ A) {
+    constexpr int NW = NT / 64;
+    __shared__ double wmin[NW];
+    __shared__ int wnan[NW];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double least = INFINITY, s[3] = {0.0, 0.0, 0.0};  // s: wave 0
+    int nan = 0;
+#pragma unroll 1
+    for (int part = 0; part < 2; ++part) {
+        const float sign = part ? -1.f : 1.f;
+        auto signed_part = [&](int k, int b) {
+            const float v = col(k, b);
+            if (v != v) nan = 1;
+            return fmaxf(sign * v, 0.f);
+        };
+        auto smallest = [&](int, double m) { least = fmin(least, m); };
+        float *Up = U + (int64_t)part * Q * n;
+        if (QM == kQuantHalf || (QM == kQuantAuto && L <= 128))
+            quantile_tiles<NT, true>(signed_part, L, n, Q, levels, TC, Ut, colS, Up, smallest);
+        else
+            quantile_tiles<NT, false>(signed_part, L, n, Q, levels, TC, Ut, colS, Up, smallest);
+        if (wave == 0) {
+            double e[3];
+            column_aux(colS, n, Q, d64, lane, e);
+            s[0] += e[0];
+            s[1] += e[1];
+            s[2] += e[2];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) least = fmin(least, __shfl_xor(least, off, 64));
+    nan = __any(nan);
+    if (lane == 0) {
+        wmin[wave] = least;
+        wnan[wave] = nan;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && A) {
+        for (int w = 1; w < NW; ++w) {
+            least = fmin(least, wmin[w]);
+            nan |= wnan[w];
+        }
+        A[0] = nan ? __longlong_as_double(0x7ff8000000000000LL) : least;
+        A[1] = s[0];
+        A[2] = 0.5 * s[1];
+        A[3] = 0.5 * s[2];
+    }
 }
 
 inline int pick_tc(int n, int Q, size_t budget) {
