@@ -285,16 +285,17 @@ __host__ __device__ inline QuantMode quant_mode_for(int L) {
 }
 
 // The scalars of one image (or signed part) from its column sums colS [n][2]
-// (sum of quantiles, sum of squares), by one wave in a fixed order: E and the
-// translation moment a in out[0..2], on every lane.
-__device__ __forceinline__ void column_aux(const double *colS, int n, int Q,
+// (sum of quantiles, sum of squares; read through get(i)), by one wave in a
+// fixed order: E and the translation moment a in out[0..2], on every lane.
+template <typename Get>
+__device__ __forceinline__ void column_aux(Get get, int n, int Q,
                                            const double2 *__restrict__ d64, int lane,
                                            double (&out)[3]) {
     double e = 0.0, x = 0.0, y = 0.0;
     for (int k = lane; k < n; k += 64) {
-        const double qbar = colS[2 * k] / (double)Q;
+        const double qbar = get(2 * k) / (double)Q;
         const double2 d = d64[k];
-        e += colS[2 * k + 1];
+        e += get(2 * k + 1);
         x += qbar * d.x;
         y += qbar * d.y;
     }
@@ -323,7 +324,7 @@ __device__ void quantile_phase(ColFn col, int L, int n, int Q, int levels, int T
         quantile_tiles<NT, false>(col, L, n, Q, levels, TC, Ut, colS, U, first);
     if (wave == 0) {
         double s[3];
-        column_aux(colS, n, Q, d64, lane, s);
+        column_aux([&](int i) { return colS[i]; }, n, Q, d64, lane, s);
         if (lane == 0 && A) {
             A[0] = mass0;  // column 0 is inverted by wave 0
             A[1] = s[0];
@@ -365,7 +366,7 @@ __device__ void quantile_phase_rf(ColFn col, int L, int n, int Q, int levels, in
             quantile_tiles<NT, false>(signed_part, L, n, Q, levels, TC, Ut, colS, Up, smallest);
         if (wave == 0) {
             double e[3];
-            column_aux(colS, n, Q, d64, lane, e);
+            column_aux([&](int i) { return colS[i]; }, n, Q, d64, lane, e);
             s[0] += e[0];
             s[1] += e[1];
             s[2] += e[2];

@@ -1057,10 +1057,14 @@ sw_status sw_tables(void *ctx, const float *img, int64_t N, const sw_geom *g, fl
     if ((st = get_plan(c, geo.L, geo.n, &pp)) != SW_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     // Fewer images than compute units: one block per image would leave most
-    // of the device idle, so project with one block per (image, task group)
-    // and invert with 16 waves per image, through scratch.
-    const bool small = c->small(N);
-    if (!small && sw::tables_fused_fits(geo)) {
+    // of the device idle, so the projection and the columns of an image are
+    // spread over blocks, through scratch.  Where a fused block has 16 waves of
+    // large images, it is the faster of the two from half as many on (128 images
+    // at L = 256, n = 128: 171 us split, 169 fused; 255: 324 and 175).
+    const bool fused = sw::tables_fused_fits(geo);
+    const bool small = fused && geo.L > 192 && c->small_batch < 0 ? N < c->cu_count / 2
+                                                                  : c->small(N);
+    if (!small && fused) {
         hipError_t e = sw::launch_tables(img, N, geo, *t, *pp, qt, aux, s, c->tables_per_block);
         return e == hipSuccess ? SW_OK : hip_fail(e, "k_tables launch");
     }
