@@ -149,8 +149,8 @@ __device__ __forceinline__ void store_gamma128(float2 *gam, float2 *gx, int p, i
 // integer divisions here), the transforms and the rescore.  Sharing the image's
 // transforms between references takes the transforms, two thirds of a pair's
 // work at n = 64, out of all but one of them.  16 x 2,000 pairs at L = n = Q = 64
-// 517 -> 199 us; one reference against 1,500 images at 256 508 -> 452 us, against
-// 1,031 at L = 39 22 -> 19 us.
+// 517 -> 142 us; one reference against 1,500 images at 256 508 -> 322 us, against
+// 1,031 at L = 39 22 -> 18 us.
 struct PairsJob {
     const float *U, *V;    // [nr][Q][n] and [Q][n] tables
     const double *au, *av; // aux of both, [nr][4] and [4]
@@ -162,13 +162,18 @@ struct PairsJob {
     int status;            // 3: bad pair index (nr is 1; nothing is read)
 };
 
-constexpr int kAlignSlots = 8;  // candidates rescored at a time (>= kMaxTopK)
+constexpr int kAlignSlots = 4;  // candidates rescored at a time (eight spill registers)
 
-// LDS of align_pairs_block in bytes: the angle table, the two FFT buffers,
-// the spectral sums and D* of every reference.
+// LDS of align_pairs_block: the angle table, then the two FFT buffers, the
+// spectral sums and D* of every reference; the rescore has rows of the image
+// table in all of it behind the angle table, at least 20 rows up to n = 256.
+__host__ __device__ inline int align_work_floats(int n, int RG) {
+    const int work = 4 * kFftElems + 2 * RG * (n / 2 + 2) + 2 * RG * n;
+    const int rows = n <= 64 ? 4352 : n <= 256 ? 20 * n : 12 * n;
+    return work > rows ? work : rows;
+}
 __host__ __device__ inline size_t align_pairs_lds(int n, int RG) {
-    return sizeof(float2) * (size_t)(n + 2 * kFftElems + RG * (n / 2 + 2)) +
-           sizeof(double) * (size_t)(RG * n);
+    return sizeof(float2) * (size_t)n + sizeof(float) * (size_t)align_work_floats(n, RG);
 }
 
 template <int NT, int RG>
@@ -390,14 +395,27 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
     __syncthreads();
 
     // --- FP32 rescore of the candidates: direct residual sums, kAlignSlots of
-    // the nr K candidates at a time.  Rows of V pass through LDS (the FFT
-    // buffers, free by now): every element is read once from memory per batch
-    // of candidates and once per candidate from LDS.
+    // the nr K candidates at a time.  RS rows of V at a time lie in LDS column
+    // by column, RP / 4 an odd number of 16-byte groups per column, so that a
+    // candidate's four rows at the lag's column are one conflict-free b128 read
+    // from an address that only advances with the rows; a thread keeps its
+    // column, with the translation's term and the column's offset of every
+    // candidate, and takes every G2-th group of four rows.  (One element a step
+    // took ten instructions a candidate, most of them indices; now four and a
+    // quarter of a read: the pairs above took 199, 452 and 18 us with that.)
     float *Vs = (float *)Z0;
-    const int RS = 4 * kFftElems / n, slots = nr * K;
+    const int slots = nr * K;
     const float in = __builtin_amdgcn_rcpf((float)n), iK = __builtin_amdgcn_rcpf((float)K);
-    const int j_0 = div_small(tid, in), k_0 = tid - __mul24(j_0, n);
-    const int dk = NT % n;  // uniform
+    const int jg = div_small(tid, in), k_0 = tid - __mul24(jg, n);
+    const int G2 = n < NT ? NT / n : 1;
+    int RS, RP;  // uniform; Q is a multiple of 4
+    {
+        int most = align_work_floats(n, RG) / n & ~3;
+        if (!(most & 4)) most -= 4;
+        const int chunks = (Q + most - 1) / most;
+        RS = ((Q + chunks - 1) / chunks + 3) & ~3;
+        RP = RS & 4 ? RS : RS + 4;
+    }
     auto rescore = [&](auto count, int c0, int nb) {
         constexpr int NB = decltype(count)::value;
         float part[NB];
@@ -412,28 +430,51 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
             sh[c] = shiftS[q];
         }
         for (int j0 = 0; j0 < Q; j0 += RS) {
-            const int cnt = min(RS, Q - j0) * n;
-            const float *Vg = job.V + (int64_t)j0 * n;
-            __syncthreads();
-            for (int idx = tid; idx < cnt; idx += NT) Vs[idx] = Vg[idx];
-            __syncthreads();
+            const int quads = min(RS, Q - j0) >> 2;
+            if (RS < Q || c0 == 0) {  // else V is there already
+                const float *Vg = job.V + (int64_t)j0 * n;
+                __syncthreads();
+                if (jg < G2)
+                    for (int k = k_0; k < n; k += NT)
+                        for (int q = jg; q < quads; q += G2) {
+                            const float *v = Vg + __mul24(4 * q, n) + k;
+                            *(float4 *)(Vs + __mul24(k, RP) + 4 * q) =
+                                make_float4(v[0], v[n], v[2 * n], v[3 * n]);
+                        }
+                __syncthreads();
+            }
+            if (jg >= G2) continue;  // no barrier but those every thread meets
             const float *Ug = job.U + (int64_t)j0 * n;
-            int k = k_0;
-            for (int idx = tid; idx < cnt; idx += NT) {
+            for (int k = k_0; k < n; k += NT) {
                 const float2 d = tw[k];
-                const float *vrow = Vs + (idx - k);
-                float u = 0.f;
+                float t[NB];
+                const float *vc[NB];
 #pragma unroll
                 for (int c = 0; c < NB; ++c) {
-                    if (c == 0 || ref[c] != ref[c - 1])  // uniform
-                        u = Ug[(int64_t)ref[c] * Q * n + idx];
                     int kk = k + lag[c];
                     if (kk >= n) kk -= n;
-                    const float e = u - vrow[kk] - (sh[c].x * d.x + sh[c].y * d.y);
-                    part[c] += e * e;
+                    vc[c] = Vs + __mul24(kk, RP);
+                    t[c] = sh[c].x * d.x + sh[c].y * d.y;
                 }
-                k += dk;
-                if (k >= n) k -= n;
+                auto quad = [&](int q) {
+                    float u[4];
+                    const unsigned o = __mul24(4 * q, n) + k;
+#pragma unroll
+                    for (int c = 0; c < NB; ++c) {
+                        if (c == 0 || ref[c] != ref[c - 1]) {  // uniform
+                            const float *p = Ug + (int64_t)ref[c] * Q * n;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) u[i] = p[o + i * n];
+                        }
+                        const float4 v = *(const float4 *)(vc[c] + 4 * q);
+                        const float e0 = u[0] - v.x - t[c], e1 = u[1] - v.y - t[c];
+                        const float e2 = u[2] - v.z - t[c], e3 = u[3] - v.w - t[c];
+                        // in pairs: a quarter of the roundings in the long sum
+                        part[c] += fmaf(e1, e1, e0 * e0) + fmaf(e3, e3, e2 * e2);
+                    }
+                };
+#pragma unroll 1
+                for (int q = jg; q < quads; q += G2) quad(q);
             }
         }
 #pragma unroll
@@ -453,8 +494,7 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
     for (int c0 = 0; c0 < slots; c0 += kAlignSlots) {
         const int nb = min(kAlignSlots, slots - c0);
         if (nb == 1) rescore(std::integral_constant<int, 1>{}, c0, nb);
-        else if (nb <= 4) rescore(std::integral_constant<int, 4>{}, c0, nb);
-        else rescore(std::integral_constant<int, 8>{}, c0, nb);
+        else rescore(std::integral_constant<int, kAlignSlots>{}, c0, nb);
     }
     __syncthreads();
     if (tid < nr && (live >> tid & 1)) {

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(NT) void k_spectrum(const float *__restrict__ qt, i
 // One block per image and run of `rg` references (all pairs), or per listed
 // pair (rg = 1).
 template <int NT, int RG>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(RG == 1 ? 7 : 5, 8))) void k_align_pairs(PairArgs a, Geo g, int rg,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(RG == 1 ? 6 : 5, 8))) void k_align_pairs(PairArgs a, Geo g, int rg,
                                                     const float2 *__restrict__ tw32,
                                                     const double2 *__restrict__ tw64) {
     extern __shared__ __align__(16) float2 lds2[];
