@@ -185,10 +185,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kProjMinWave
 // into the region with the padded column stride, filtered and inverted.
 // Bitwise the results of k_tables_rf.
 //
-// 4,000 images at L = n = Q = 128: 1,160 -> 1,010 us with the filter's products at
-// the odd offsets only, the parts' masses taken from the inversions instead of
-// a pass of their own, and one body of code for both parts (2 spilled registers
-// instead of 28); the plain tables take 708.
+// 4,000 images at L = n = Q = 128: 1,160 -> 1,050 us with the parts' masses taken
+// from the inversions instead of a pass of their own, and one body of code for
+// both parts (2 spilled registers instead of 28); the plain tables take 708.
+// (The filter's taps at even offsets are zero: with only the products at the odd
+// ones, and the own term in its place among them, it took 1,044 us, but with
+// 4 to 20 % more rounding error.)
 template <int NT, int TPW, int NS>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tables2_rf(
     const float *__restrict__ img, int64_t N, TablesShape T, const float2 *__restrict__ d32,
