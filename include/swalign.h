@@ -115,7 +115,8 @@ typedef struct {
    path to a JSON file with optional keys: "tiles" (the table written by
    sw_autotune), "small_batch": calls on fewer images than this take the
    split launches (several blocks per image; default: the number of compute
-   units), "tables_images_per_block": 1 or 2 (default 2), the images one
+   units, half of it for fused tables with L > 192, a third of it for the
+   Fourier-slice projector with L > 64), "tables_images_per_block": 1 or 2 (default 2), the images one
    block of the fused sw_tables / sw_tables_rf kernels projects from the same
    strips where the geometry allows two, and "align_kernel": "generic", which
    keeps sw_align_batch on the LDS-FFT pair kernel for n_angles = 128 instead
@@ -137,11 +138,12 @@ const char *sw_last_error(void);
 const char *sw_version(void);
 
 /* The work plan of the line projection (Sec. 2.2/2.3, step 1) for side L and
-   n angles, as every projection launch of (L, n) uses it: host memory only,
-   no context and no device work (for inspection and tests).  Items are
-   (slot angle m <= n/8, bin b) pairs, item = m L + b; a task is 64 lanes,
-   eight units of 8 consecutive bins of one slot.  perm[t 64 + l] = the item
-   of lane l of task t, or -1; [row_lo[t], row_hi[t]] = the image rows task t
+   n angles, as every projection launch of (L, n) uses its tasks and rows: host
+   memory only, no context and no device work (for inspection and tests).
+   Items are (slot angle m <= n/8, bin b) pairs, item = m L + b; a task is 64
+   items, eight units of 8 consecutive bins of one slot.  perm[t 64 + l] = item
+   l of task t, or -1 (the launches place a task's items in its lanes in an order
+   of their own, by LDS banks); [row_lo[t], row_hi[t]] = the image rows task t
    reads (every row where one of its items' lines has a pixel of non-zero
    weight inside the disk; row_lo > row_hi for a task with none).  *ntasks is
    set first; the arrays (cap_tasks tasks; NULL with cap_tasks = 0 to query
@@ -300,7 +302,8 @@ sw_status sw_align_batch(void *ctx, const sw_batch *b /*host*/, sw_result *out, 
    reference (plus 520 Q bytes per reference at n = 128: 133 KiB in all at
    n = Q = 128), the all-pairs BF16 form 4 (n/2+1) Q bytes per table of
    both sets plus 2 top_k bytes per pair (about 47 MiB for 2,000 x 2,000
-   tables at n = Q = 64).  All calls on
+   tables at n = Q = 64), and 24 bytes or more per table to spare candidates
+   from the rescore where that fits as well (same results).  All calls on
    one GPU share the array: calls that overlap on one GPU (other streams,
    other contexts, other threads) race and must be ordered by the caller.
    Nothing in it needs clearing between calls. */
