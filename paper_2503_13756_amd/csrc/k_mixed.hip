@@ -176,7 +176,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
 // Other items (work items [split, total)): LDS-FFT alignment of every image
 // against the item's reference.  Held to 72 VGPRs for seven waves per SIMD:
 // left alone the compiler takes 113 in the work loop, and the four waves that
-// leaves are slower (uneven stacks: 1.23 ms against 0.91 with 44 spills).
+// leaves are slower (uneven stacks 1.23 ms against 0.91, spills and all; 0.74
+// since the rescore takes four rows a read; six waves per SIMD the same).
 template <int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_align_mixed(const MixGroup *__restrict__ G,
                                                     unsigned long long *counter) {
