@@ -185,7 +185,10 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
     __shared__ int lagS[RG * kMaxTopK];
     __shared__ float2 shiftS[RG * kMaxTopK];
     __shared__ float valS[RG * kMaxTopK];
-    __shared__ float red[NW][kAlignSlots];
+    // the waves' sums of a batch of candidates, batches taking turns: a batch's
+    // one barrier lies between its writes and wave 0's reads, and the next
+    // batch's barrier between those reads and the next writes to the same set
+    __shared__ float red[2][NW][kAlignSlots];
     const int n = g.n, Q = g.Q, Wn = n / 2 + 1, half = n / 2, K = top_k;
     // an opaque copy of the thread index: in a persistent caller, what is
     // derived from it is formed per job instead of being kept live across jobs
@@ -418,6 +421,7 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
     }
     auto rescore = [&](auto count, int c0, int nb) {
         constexpr int NB = decltype(count)::value;
+        float(*sums)[kAlignSlots] = red[c0 / kAlignSlots & 1];
         float part[NB];
         int lag[NB], ref[NB];
         float2 sh[NB];
@@ -482,12 +486,12 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
             float v = part[c];
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-            if (lane == 0) red[wave][c] = v;
+            if (lane == 0) sums[wave][c] = v;
         }
         __syncthreads();
         if (tid < nb) {
             float t = 0.f;
-            for (int w = 0; w < NW; ++w) t += red[w][tid];
+            for (int w = 0; w < NW; ++w) t += sums[w][tid];
             valS[c0 + tid] = t / (float)nq;
         }
     };
