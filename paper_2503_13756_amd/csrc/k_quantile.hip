@@ -100,14 +100,18 @@ __global__ __launch_bounds__(NT) void k_quantile_cols(const float *__restrict__ 
     if (L <= 128) invert_tile<NT, true>(col, L, Q, levels, TC, k0, Ut, cs - 2 * k0, on_mass);
     else invert_tile<NT, false>(col, L, Q, levels, TC, k0, Ut, cs - 2 * k0, on_mass);
     __syncthreads();
-    // wave 0: the sums, and the masses of the columns (or of the parts), NaN for
-    // a NaN value
+    // wave 0: the sums, and the masses of the columns (or of the parts).  A part's
+    // mass is NaN for a NaN value, and infinite where the scan made a NaN of an
+    // infinite one (an overflowed filter), which the smallest mass leaves out as
+    // the fmin of quantile_phase_rf does.
     static_assert(2 * TC <= 64, "one wave publishes a block's sums");
     if (threadIdx.x < 2 * TC)
         publish(colS + ((g * parts + part) * n + k0) * 2 + threadIdx.x, cs[threadIdx.x]);
     if (threadIdx.x < TC)
         publish(colM + (g * parts + part) * n + k0 + threadIdx.x,
-                RF && nan ? __longlong_as_double(0x7ff8000000000000LL) : cm[threadIdx.x]);
+                !RF   ? cm[threadIdx.x]
+                : nan ? __longlong_as_double(0x7ff8000000000000LL)
+                      : fmin(cm[threadIdx.x], INFINITY));
     if (wave == 0) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores have arrived
         if (lane == 0)
