@@ -123,7 +123,9 @@ typedef struct {
    of the register-FFT one (the two agree to FP32 rounding), or "block128",
    which runs the register-FFT alignment with one pair per block instead of
    one pair per wave (same arithmetic, sums in another order).  The first
-   three change launch shapes only, never results. */
+   three change launch shapes only, never results; nor does
+   "all_pairs_rescore": "every", with which the all-pairs BF16 form rescores
+   every candidate instead of those that its error bound leaves. */
 /* Scratch: the context owns one scratch buffer (grown on demand) that the
    calls needing it share: sw_tables / sw_tables_rf when they take their
    chunked or small-batch path, sw_align_batch (except the max-sliced mode)

@@ -960,6 +960,8 @@ sw_status sw_ctx_create(void **ctx, int device, const char *tune_json) {
             c->align128_per_wave = false;
         if (std::regex_search(txt, m, std::regex("\"tables_images_per_block\"\\s*:\\s*([12])")))
             c->tables_per_block = std::stoi(m[1]);
+        if (std::regex_search(txt, m, std::regex("\"all_pairs_rescore\"\\s*:\\s*\"every\"")))
+            c->prune_pairs = false;
         if (std::regex_search(txt, m, std::regex("\"serve_fail_ticket\"\\s*:\\s*(\\d+)")))
             c->serve_fail_ticket = std::stoull(m[1]);
     }
@@ -1431,7 +1433,7 @@ static sw_status align_batch_impl(void *ctx, const sw_batch *b, sw_result *out, 
         const size_t nimg_bytes = same_set ? 0 : sizeof(float2) * sw::kSpecNorms * (size_t)b->n_img * nb_img;
         const size_t need = ref_bytes + img_bytes + sizeof(int16_t) * (size_t)P * top_k;
         const size_t with_norms = ref_bytes + img_bytes + cand_bytes + nref_bytes + nimg_bytes;
-        const bool prune = !noalloc || with_norms <= kNoAllocWorkBytes;
+        const bool prune = c->prune_pairs && (!noalloc || with_norms <= kNoAllocWorkBytes);
         void *scr;
         if ((st = take_scratch(prune ? with_norms : need, &scr)) != SW_OK) return st;
         char *base = (char *)scr;
