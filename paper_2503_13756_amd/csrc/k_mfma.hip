@@ -273,18 +273,38 @@ __global__ __launch_bounds__(256) void k_corr_mfma(const uint32_t *__restrict__ 
     // common to all lags), which Cauchy-Schwarz bounds by the tables' norms
     // weighted with g (kSpecNorms: any lags, neighbours, two apart; the
     // candidates mostly are neighbours, where g is small at the low
-    // frequencies that hold most of the energy).  The FP32 sums of X (fewer
-    // than 160 roundings of at most E = (E_U + E_V) / 2 each), the split operands
-    // of the inverse transform (3 2^-18 of the terms with w >= 1) and the
-    // rescore's own rounding come to less than kSum E + kSplit |U| |V| / n a lag.
-    // A candidate further below the largest X than that has a larger rescored
-    // objective for certain: the results are those of rescoring all top_k.
+    // frequencies that hold most of the energy).  The rest comes to less than
+    // kSum (E + W / 2) + kSplit W a lag, with u = 2^-24, E = (E_U + E_V) / 2 and
+    // W = |U| |V| / n of the norms for any lags (at least twice the sum of
+    // c_w |S_w| / n over w >= 1):
+    //  - v_mfma_f32_16x16x32_bf16 adds its products to the accumulator in four
+    //    groups of eight, each rounded to nearest once after an aligned sum
+    //    (probed: products of one group add up before they are rounded, and 1.4
+    //    million random sums were off by 1.1 u a group of the magnitudes added
+    //    at most): 3 u a group is taken here, for the 4 groups of 3 products in
+    //    every step of the inverse transform, whose magnitudes come to E + W / 2 at
+    //    most (the W / 2 for the translation in S_1);
+    //  - the FP32 transforms that both the spectra and the norms come from: a
+    //    pass is off by 5 u of its norm (twiddle product 3, two layers of
+    //    additions 2), three passes and the separation of the rows 16 u of
+    //    sqrt(n E_U), in a difference of lags 64 u E, half of it a lag;
+    //  - the rescored residual: 26 roundings (the difference's count twice, 16
+    //    steps, 8 additions across) of R0 / 2 <= 2 E, and the objective's to
+    //    FP32, 54 u E;
+    //  - in kSplit: the split operands (3 2^-18 of c_w |S_w| / n), the groups of
+    //    the 2 n products of each part of S_w, its lowering and the twiddles.
+    // A candidate further below the largest X has a larger rescored objective:
+    // the results are those of rescoring all top_k.
     int keep = top_k;
     if (norm_ref) {
-        constexpr float kSum = 1e-5f, kSplit = 2e-5f;
+        constexpr float u = 0x1p-24f, group = 3 * u;
+        constexpr int steps = (2 * Wn + 31) / 32;
+        constexpr float kSum = 4 * 3 * steps * group + (32 + 54) * u;  // 1.2e-5 at n = 64
+        constexpr float kSplit = 0.5f * (3 * 0x1p-18f + 1.42f * 4 * KS * group) + 8 * u;
         const float2 *a = nrm[t / 16], *v = nrm[16 + t % 16];
         const float E = 0.5f * (float)(ref_aux[4 * r + 1] + img_aux[4 * g + 1]);
-        const float fix = 2.f * (kSum * E + kSplit / (float)N * a[0].x * v[0].x);
+        const float W = a[0].x * v[0].x / (float)N;
+        const float fix = 2.f * (kSum * (E + 0.5f * W) + kSplit * W);
         float T[kSpecNorms];
 #pragma unroll
         for (int j = 0; j < kSpecNorms; ++j)

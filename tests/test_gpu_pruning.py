@@ -64,6 +64,31 @@ def test_records_of_every_candidate(contexts, n, refs, count, mode, top_k):
     assert torch.equal(res[0], res[1])
 
 
+@pytest.mark.parametrize("n", [32, 64])
+@pytest.mark.parametrize("eps", [1e-2, 1e-3, 1e-4, 1e-5])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_records_of_almost_flat_curves(contexts, n, eps, mode):
+    """Tables of one quantile function whose columns differ by eps: the lags'
+    objectives lie within the roundings of sums that are 1 / eps^2 larger."""
+    import torch
+    from paper_2503_13756_amd import api
+
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    base = torch.linspace(-0.9, 0.9, n, device="cuda")[:, None]
+    noise = torch.randn(500, n, n, generator=gen, device="cuda")
+    q = (base + eps * noise.sort(dim=1).values).contiguous()
+    d = q.double()
+    th = 2 * np.pi * torch.arange(n, device="cuda", dtype=torch.float64) / n
+    m = d.mean(1)
+    a = torch.stack([torch.ones(500, dtype=torch.float64, device="cuda"), (d * d).sum((1, 2)),
+                     (m * th.cos()).mean(1), -(m * th.sin()).mean(1)], 1).contiguous()
+    res = [api.align_batch(ctx, q[:200].contiguous(), a[:200].contiguous(), q[200:].contiguous(),
+                           a[200:].contiguous(), n, mode=mode, prec=1, top_k=4)[0]
+           for ctx in contexts]
+    assert torch.equal(res[0], res[1])
+
+
 @pytest.mark.parametrize("n,count", [(64, 2026), (32, 2636)])
 def test_scratch_between_the_two_needs(contexts, n, count):
     """The counts at which the no-alloc scratch holds what rescoring every
