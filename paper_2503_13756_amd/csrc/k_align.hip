@@ -3,6 +3,7 @@
 #include <algorithm>
 
 #include "align_dev.h"
+#include "wave_dev.h"
 
 namespace sw {
 
@@ -53,8 +54,8 @@ __global__ __launch_bounds__(NT) void k_spectrum(const float *__restrict__ qt, i
                               const float a =
                                   cw * (xe.x * xe.x + xe.y * xe.y + xo.x * xo.x + xo.y * xo.y);
                               const float b = cw * (ex * ex + ey * ey + dx * dx + dy * dy);
-                              const float gw[kSpecNorms] = {2.f, sqrtf(2.f - 2.f * t.x),
-                                                            2.f * fabsf(t.y)};
+                              const float gw[kSpecNorms] = {
+                                  2.f, __builtin_amdgcn_sqrtf(2.f - 2.f * t.x), 2.f * fabsf(t.y)};
 #pragma unroll
                               for (int i = 0; i < kSpecNorms; ++i) {
                                   sq[i].x += gw[i] * a;
@@ -66,12 +67,8 @@ __global__ __launch_bounds__(NT) void k_spectrum(const float *__restrict__ qt, i
             __shared__ float2 ws[NT / 64][kSpecNorms];
 #pragma unroll
             for (int i = 0; i < kSpecNorms; ++i) {
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) {
-                    sq[i].x += __shfl_xor(sq[i].x, off, 64);
-                    sq[i].y += __shfl_xor(sq[i].y, off, 64);
-                }
-                if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6][i] = sq[i];
+                const float2 sum = make_float2(wave_sum_f(sq[i].x), wave_sum_f(sq[i].y));
+                if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6][i] = sum;
             }
             __syncthreads();
             if (threadIdx.x < kSpecNorms) {

@@ -27,6 +27,7 @@
 // prove not to be the minimum (1.24 of 4 are left on noisy copies of one
 // object): 2,000 x 2,000 at L = 64 5.44 -> 2.54 ms.
 #include "sw_internal.h"
+#include "wave_dev.h"
 
 namespace sw {
 
@@ -71,24 +72,6 @@ __global__ __launch_bounds__(256) void k_corr_mfma(const uint32_t *__restrict__ 
     if (it * 16 >= n_img) return;  // block-uniform, before any barrier
     const int64_t g0 = it * 16, r0 = rt * 16;
     for (int i = threadIdx.x; i < N; i += 256) tw[i] = tw32[i];
-    // norms of the tile's spectra (references, then images) for the pruning
-    __shared__ float2 nrm[32][kSpecNorms];
-    if (norm_ref && threadIdx.x < 32 * kSpecNorms) {
-        const int e = threadIdx.x / kSpecNorms, j = threadIdx.x - kSpecNorms * e;
-        const bool ref = e < 16;
-        const int64_t k = ref ? r0 + e : g0 + e - 16;
-        const float2 *src = ref ? norm_ref : norm_img;
-        const int nb = ref ? nb_ref : nb_img;
-        float2 q = make_float2(0.f, 0.f);
-        if (k < (ref ? n_ref : n_img))
-            for (int i = 0; i < nb; ++i) {
-                const float2 v = src[(k * nb + i) * kSpecNorms + j];
-                q.x += v.x;
-                q.y += v.y;
-            }
-        nrm[e][j] = make_float2(sqrtf(q.x), sqrtf(q.y));
-    }
-
     // Spectral products on the gfx950 bf16 MFMA with 32 K entries (16
     // complex values) per instruction: lane l holds row l % 16 (reference)
     // or column l % 16 (image) and the complex values 16 s + 4 (l / 16) ..
@@ -109,12 +92,44 @@ __global__ __launch_bounds__(256) void k_corr_mfma(const uint32_t *__restrict__ 
             B[s] = pb[(int64_t)w * (N / 4) + 4 * s];
         }
     };
+    fetch(wave, a_cur, b_cur);  // wave < 4 < Wn
+    // norms of the tile's spectra (references, then images) for the pruning, by
+    // the last two waves, while the first frequency's spectra are on their way
+    __shared__ float2 nrm[32][kSpecNorms];
+    const int en = (int)threadIdx.x - 128;
+    if (norm_ref && en >= 0 && en < 32 * kSpecNorms) {
+        const int e = en / kSpecNorms, j = en - kSpecNorms * e;
+        const bool ref = e < 16;
+        const int64_t k = ref ? r0 + e : g0 + e - 16;
+        const float2 *src = ref ? norm_ref : norm_img;
+        const int nb = ref ? nb_ref : nb_img;
+        float2 sum = make_float2(0.f, 0.f);
+        if (k < (ref ? n_ref : n_img)) {
+            // the partial sums of few tables are many: sixteen loads in flight
+            // (one at a time they were 5 us of a call on one reference at n = 64)
+            constexpr int kLoads = 16;
+            src += k * nb * kSpecNorms + j;
+            for (int i0 = 0; i0 < nb; i0 += kLoads) {
+                float2 v[kLoads];
+#pragma unroll
+                for (int i = 0; i < kLoads; ++i)
+                    if (i0 + i < nb) v[i] = src[(i0 + i) * kSpecNorms];
+#pragma unroll
+                for (int i = 0; i < kLoads; ++i)
+                    if (i0 + i < nb) {
+                        sum.x += v[i].x;
+                        sum.y += v[i].y;
+                    }
+            }
+        }
+        nrm[e][j] = make_float2(sqrtf(sum.x), sqrtf(sum.y));
+    }
+
     // Fully unrolled over this wave's frequencies w = wave + 4 i: every fetch
     // is issued (the one past the last frequency refetches it), so exactly
     // one frequency's fetch is in flight while the previous one is
     // multiplied.
     constexpr int NI = (Wn + 3) / 4;
-    fetch(wave, a_cur, b_cur);  // wave < 4 < Wn
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         const int w = wave + 4 * i;
@@ -332,24 +347,6 @@ __global__ __launch_bounds__(256) void k_corr_mfma(const uint32_t *__restrict__ 
     int16_t *out = cand + (r * n_img + g) * (int64_t)top_k;
     for (int c = 0; c < top_k; ++c)
         out[c] = c < keep ? (int16_t)(top[c] & (uint32_t)(N - 1)) : (int16_t)-1;
-}
-
-// Sum over the 64 lanes: butterflies inside each row of 16 lanes on DPP,
-// then the four row totals.  Fixed order, so the result is deterministic.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float wave_sum_f(float v) {
-    v += dpp_f<0xb1>(v);   // quad_perm [1,0,3,2]
-    v += dpp_f<0x4e>(v);   // quad_perm [2,3,0,1]
-    v += dpp_f<0x141>(v);  // row_half_mirror
-    v += dpp_f<0x140>(v);  // row_mirror
-    const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-    const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-    const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-    const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-    return (r0 + r1) + (r2 + r3);
 }
 
 // Rescore: grid (ceil(n_img / (NT / 64)), ceil(n_ref / TR)), NT threads; wave w owns
