@@ -20,6 +20,7 @@
 #pragma once
 #include <type_traits>
 #include "fft_dev.h"
+#include "wave_dev.h"
 
 namespace sw {
 
@@ -62,18 +63,11 @@ __device__ __forceinline__ void unpack(const float2 *Z, int pl, int n, int w, fl
 }
 
 __device__ __forceinline__ int fft_chunk_rows(int n, int Q) {
-    const int c = kFftElems / n;
+    const int c = div_uniform(kFftElems, n);
     return c < Q / 2 ? c : Q / 2;
 }
 
 // -------------------------------------------------------------- alignment
-__device__ __forceinline__ void argmin_merge(double &v, int &i, double v2, int i2) {
-    if (v2 < v || (v2 == v && i2 < i)) {
-        v = v2;
-        i = i2;
-    }
-}
-
 // b(l) = a_U - e^{i theta_l} a_V
 __device__ __forceinline__ double2 trans_moment(const double *au, const double *av, double2 d) {
     const double c = d.x, s = -d.y;
@@ -237,13 +231,14 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
 
     // --- spectra of V and the spectral dots with conj(U^).  Thread (gg, w),
     // w fastest, sums the packed rows gg, gg + G, .. of every chunk.
-    const int G = Wn >= NT ? 1 : NT / Wn, items = Wn * G;
+    const float iW = __builtin_amdgcn_rcpf((float)Wn);
+    const int G = Wn >= NT ? 1 : div_uniform(NT, Wn), items = Wn * G;
     float2 s[IT][RG];
 #pragma unroll
     for (int i = 0; i < IT; ++i)
 #pragma unroll
         for (int r = 0; r < RG; ++r) s[i][r] = make_float2(0.f, 0.f);
-    const int gg0 = div_small(tid, __builtin_amdgcn_rcpf((float)Wn));
+    const int gg0 = div_small(tid, iW);
     const int CH = fft_chunk_rows(n, Q);
     const int64_t specs = (int64_t)(Q / 2) * Wn;  // of one reference
     for (int p0 = 0; p0 < Q / 2; p0 += CH) {
@@ -301,11 +296,10 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
             if (r < nr && it < items) Sacc[r * items + it] = s[i][r];
     }
     __syncthreads();
-    const float iW = __builtin_amdgcn_rcpf((float)Wn);
     for (int x = tid; x < nr * Wn; x += NT) {
         const int r = div_small(x, iW), w = x - __mul24(r, Wn);
         float2 t = make_float2(0.f, 0.f);
-        for (int gg = 0; gg < G; ++gg) {
+        for (int gg = 0; gg < min(G, CH); ++gg) {  // further groups had no rows
             const float2 v = Sacc[r * items + __mul24(gg, Wn) + w];
             t.x += v.x;
             t.y += v.y;
@@ -317,9 +311,10 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
     // --- inverse transform over w.  Lags l and l + n/2 share every twiddle up
     // to the sign (-1)^w, so one sum over even w and one over odd w gives both;
     // the w range is cut in `parts` so that every thread has a share.
-    const int parts = min(8, max(1, NT / half)), len = (half - 1 + parts - 1) / parts;
-    float2 *ps = Z0;  // [parts][nr][half] (even, odd)
     const float ih = __builtin_amdgcn_rcpf((float)half);
+    const int parts = min(8, max(1, div_uniform(NT, half)));
+    const int len = div_uniform(half - 2 + parts, parts);
+    float2 *ps = Z0;  // [parts][nr][half] (even, odd)
     const float ir = __builtin_amdgcn_rcpf((float)nr);
     for (int x = tid; x < parts * nr * half; x += NT) {
         const int pr = div_small(x, ih), l = x - __mul24(pr, half);
@@ -376,12 +371,7 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
             double v = __builtin_inf();
             int i = 0x7fffffff;
             for (int l = lane; l < n; l += 64) argmin_merge(v, i, Dr[l], l);
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                const double v2 = __shfl_xor(v, off, 64);
-                const int i2 = __shfl_xor(i, off, 64);
-                argmin_merge(v, i, v2, i2);
-            }
+            wave_argmin(v, i);
             if (i >= n) i = 0;  // every D* is NaN
             if (lane == 0) {
                 Dr[i] = __builtin_inf();
@@ -410,13 +400,13 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
     const int slots = nr * K;
     const float in = __builtin_amdgcn_rcpf((float)n), iK = __builtin_amdgcn_rcpf((float)K);
     const int jg = div_small(tid, in), k_0 = tid - __mul24(jg, n);
-    const int G2 = n < NT ? NT / n : 1;
+    const int G2 = n < NT ? div_uniform(NT, n) : 1;
     int RS, RP;  // uniform; Q is a multiple of 4
     {
-        int most = align_work_floats(n, RG) / n & ~3;
+        int most = div_uniform(align_work_floats(n, RG), n) & ~3;
         if (!(most & 4)) most -= 4;
-        const int chunks = (Q + most - 1) / most;
-        RS = ((Q + chunks - 1) / chunks + 3) & ~3;
+        const int chunks = div_uniform(Q + most - 1, most);
+        RS = (div_uniform(Q + chunks - 1, chunks) + 3) & ~3;
         RP = RS & 4 ? RS : RS + 4;
     }
     auto rescore = [&](auto count, int c0, int nb) {
@@ -483,9 +473,7 @@ __device__ void align_pairs_block(const PairsJob &job, Geo g, int mode, int bf16
         }
 #pragma unroll
         for (int c = 0; c < NB; ++c) {
-            float v = part[c];
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+            const float v = wave_butterfly_sum(part[c]);
             if (lane == 0) sums[wave][c] = v;
         }
         __syncthreads();

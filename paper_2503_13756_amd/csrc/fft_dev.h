@@ -42,6 +42,11 @@ __device__ __forceinline__ void dft_small(float2 (&a)[R]) {
 __device__ __forceinline__ int div_small(int x, float inv) {
     return (int)(((float)x + 0.5f) * inv);
 }
+// The same of wave-uniform x and d, as a scalar: an integer division of two
+// scalars is some twenty vector instructions.
+__device__ __forceinline__ int div_uniform(int x, int d) {
+    return __builtin_amdgcn_readfirstlane(div_small(x, __builtin_amdgcn_rcpf((float)d)));
+}
 
 // One Stockham pass of radix R over `rows` complex rows of length n, from X
 // to Y (row stride rs).  p = product of the radices already applied.  The
@@ -52,8 +57,8 @@ __device__ __forceinline__ void fft_pass(const float2 *X, float2 *Y, int rows, i
                                          int p, const float2 *tw) {
     const int nr = n / R;
     const int nb = rows * nr;
-    const int ts = n / (p * R);
     const float inr = __builtin_amdgcn_rcpf((float)nr), ip = __builtin_amdgcn_rcpf((float)p);
+    const int ts = div_uniform(nr, p);
     for (int idx = threadIdx.x; idx < nb; idx += NT) {
         const int row = div_small(idx, inr), i = idx - __mul24(row, nr);
         const int k = i - __mul24(div_small(i, ip), p);
@@ -81,7 +86,7 @@ __device__ __forceinline__ void fft_pass(const float2 *X, float2 *Y, int rows, i
 template <int NT>
 __device__ float2 *fft_rows(float2 *A, float2 *B, int rows, int n, int rs, int p,
                             const float2 *tw) {
-    int m = n / p;
+    int m = div_uniform(n, p);
     float2 *x = A, *y = B;
     while (m % 4 == 0) {
         fft_pass<NT, 4>(x, y, rows, n, rs, p, tw);

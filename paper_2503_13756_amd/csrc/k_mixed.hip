@@ -174,12 +174,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
 }
 
 // Other items (work items [split, total)): LDS-FFT alignment of every image
-// against the item's reference.  Held to 72 VGPRs for seven waves per SIMD:
-// left alone the compiler takes 113 in the work loop, and the four waves that
-// leaves are slower (uneven stacks 1.23 ms against 0.91, spills and all; 0.74
-// since the rescore takes four rows a read; six waves per SIMD the same).
+// against the item's reference.  Held to 80 VGPRs for six waves per SIMD: left
+// alone the compiler takes 113 in the work loop, and the four waves that leaves
+// are slower (uneven stacks 1.23 ms against 0.91 then).  The uneven stacks take
+// 0.71 ms with six, 0.78 with seven, whose spills reach the rescore, and 0.73
+// with five, which are faster for small images (2,000 at L = 16, eight
+// candidates, 146, 155 and 137 us a call).
 template <int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_align_mixed(const MixGroup *__restrict__ G,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_align_mixed(const MixGroup *__restrict__ G,
                                                     unsigned long long *counter) {
     extern __shared__ __align__(16) float2 lds2[];
     __shared__ int64_t wslot;

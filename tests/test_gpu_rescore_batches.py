@@ -8,10 +8,10 @@ pytestmark = pytest.mark.gpu
 
 
 # a batch is four candidates.  All Q rows of the image table in LDS at once, so
-# that no staging lies between two batches, with one lag block, the sizes of a
-# lone pair and of digits; and (96, 96, 96), staged in several chunks
+# that no staging lies between two batches, down to fewer lags than lanes and up
+# to the most; and (96, 96, 96), staged in several chunks
 @pytest.mark.parametrize("L,n,Q", [(16, 16, 16), (24, 24, 20), (39, 48, 48), (64, 64, 64),
-                                   (96, 96, 96)])
+                                   (96, 96, 96), (16, 8, 8), (64, 512, 8)])
 @pytest.mark.parametrize("top_k", [5, 8])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_batches_of_candidates_agree(oracle, L, n, Q, top_k, mode):
