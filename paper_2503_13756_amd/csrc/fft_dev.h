@@ -49,16 +49,15 @@ __device__ __forceinline__ int div_uniform(int x, int d) {
 }
 
 // One Stockham pass of radix R over `rows` complex rows of length n, from X
-// to Y (row stride rs).  p = product of the radices already applied.  The
-// indices are quotients by n / R and by p, which integer division would make
-// most of the pass's instructions.
+// to Y (row stride rs).  p = product of the radices already applied, ts = n /
+// (p R).  The indices are quotients by n / R and by p, which integer division
+// would make most of the pass's instructions.
 template <int NT, int R>
 __device__ __forceinline__ void fft_pass(const float2 *X, float2 *Y, int rows, int n, int rs,
-                                         int p, const float2 *tw) {
+                                         int p, int ts, const float2 *tw) {
     const int nr = n / R;
     const int nb = rows * nr;
     const float inr = __builtin_amdgcn_rcpf((float)nr), ip = __builtin_amdgcn_rcpf((float)p);
-    const int ts = div_uniform(nr, p);
     for (int idx = threadIdx.x; idx < nb; idx += NT) {
         const int row = div_small(idx, inr), i = idx - __mul24(row, nr);
         const int k = i - __mul24(div_small(i, ip), p);
@@ -86,21 +85,24 @@ __device__ __forceinline__ void fft_pass(const float2 *X, float2 *Y, int rows, i
 template <int NT>
 __device__ float2 *fft_rows(float2 *A, float2 *B, int rows, int n, int rs, int p,
                             const float2 *tw) {
-    int m = div_uniform(n, p);
+    int m = n / p;  // p is 1 or 4 where it is called
     float2 *x = A, *y = B;
     while (m % 4 == 0) {
-        fft_pass<NT, 4>(x, y, rows, n, rs, p, tw);
-        p *= 4; m /= 4;
+        m /= 4;
+        fft_pass<NT, 4>(x, y, rows, n, rs, p, m, tw);
+        p *= 4;
         float2 *t = x; x = y; y = t;
     }
     while (m % 3 == 0) {
-        fft_pass<NT, 3>(x, y, rows, n, rs, p, tw);
-        p *= 3; m /= 3;
+        m /= 3;
+        fft_pass<NT, 3>(x, y, rows, n, rs, p, m, tw);
+        p *= 3;
         float2 *t = x; x = y; y = t;
     }
     while (m % 2 == 0) {
-        fft_pass<NT, 2>(x, y, rows, n, rs, p, tw);
-        p *= 2; m /= 2;
+        m /= 2;
+        fft_pass<NT, 2>(x, y, rows, n, rs, p, m, tw);
+        p *= 2;
         float2 *t = x; x = y; y = t;
     }
     return x;

@@ -47,7 +47,8 @@ __host__ __device__ inline int fourier_ring(int L) { return L <= 36 ? L + 7 : 2 
 __host__ __device__ inline bool fourier_tail(int L) { return L > 64; }  // a step of its own
 inline int fourier_threads(int L) { return L <= 128 ? 512 : 1024; }
 __host__ __device__ inline int fourier_rounds(int L) {
-    return (L + fourier_group(L) - 1) / fourier_group(L);
+    const int G = fourier_group(L);  // a power of two
+    return (L + G - 1) >> __builtin_ctz((unsigned)G);
 }
 __host__ __device__ inline int fourier_slices(const FourierShape &S) {
     return S.mirror ? S.n / 2 : S.n;

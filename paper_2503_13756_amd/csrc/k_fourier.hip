@@ -134,56 +134,61 @@ __device__ __forceinline__ void first_step(float2 *dst, int j, float2 x, float2 
     d[1] = make_float4(x.x - y.x, x.y - y.y, x.x + y.y, x.y - y.x);
 }
 
-// Slice values yhat at the points i0 .. i1 - 1 of the table, whose columns are
-// in the ring (column v in slot v mod RC, row stride CS).  A point's entry
+// Slice value yhat at a point of the table whose columns are in the ring (column
+// v in slot v mod RC, row stride CS).  A point's entry
 // (host-built per geometry, float4 x 5): (first row u0, slot of its first
 // column | conj << 16) as ints and the complex factor (pixel-centre phase times
 // the cell transform); the kW x-weights and the point's index in Y; the kW
 // y-weights.  With conj the kernel was evaluated at the mirrored point and the
 // sum is conjugated.
-template <int NT>
-__device__ __forceinline__ void slice_points(const float2 *ring, int CS, int RC,
-                                             const float4 *__restrict__ T, int npts, int i0, int i1,
-                                             float2 *__restrict__ Y) {
-    for (int i = i0 + (int)threadIdx.x; i < i1; i += NT) {
-        const float4 e0 = T[i], e1 = T[npts + i], e2 = T[2 * npts + i], e3 = T[3 * npts + i],
-                     e4 = T[4 * npts + i];
-        const int vw = __float_as_int(e0.y);
-        const float wx[kFourierW] = {e1.x, e1.y, e1.z, e1.w, e2.x, e2.y, e2.z};
-        const float wy[kFourierW] = {e3.x, e3.y, e3.z, e3.w, e4.x, e4.y, e4.z};
-        int s = vw & 0xffff;
-        const float2 *row = ring + __float_as_int(e0.x);
-        float2 acc = make_float2(0.f, 0.f);
+struct Point {
+    float4 e[5];
+};
+__device__ __forceinline__ Point load_point(const float4 *__restrict__ T, int npts, int i) {
+    return Point{{T[i], T[npts + i], T[2 * npts + i], T[3 * npts + i], T[4 * npts + i]}};
+}
+__device__ __forceinline__ void slice_point(const float2 *ring, int CS, int RC, const Point &p,
+                                            float2 *__restrict__ Y) {
+    const float4 e0 = p.e[0], e1 = p.e[1], e2 = p.e[2], e3 = p.e[3], e4 = p.e[4];
+    const int vw = __float_as_int(e0.y);
+    const float wx[kFourierW] = {e1.x, e1.y, e1.z, e1.w, e2.x, e2.y, e2.z};
+    const float wy[kFourierW] = {e3.x, e3.y, e3.z, e3.w, e4.x, e4.y, e4.z};
+    int s = vw & 0xffff;
+    const float2 *row = ring + __float_as_int(e0.x);
+    float2 acc = make_float2(0.f, 0.f);
 #pragma unroll
-        for (int c = 0; c < kFourierW; ++c) {
-            const float2 *col = row + __mul24(s, CS);
-            float2 ra = make_float2(0.f, 0.f);
+    for (int c = 0; c < kFourierW; ++c) {
+        const float2 *col = row + __mul24(s, CS);
+        float2 ra = make_float2(0.f, 0.f);
 #pragma unroll
-            for (int a = 0; a < kFourierW; ++a) {
-                const float2 bv = col[a];
-                ra.x = fmaf(wy[a], bv.x, ra.x);
-                ra.y = fmaf(wy[a], bv.y, ra.y);
-            }
-            acc.x = fmaf(wx[c], ra.x, acc.x);
-            acc.y = fmaf(wx[c], ra.y, acc.y);
-            s = (s + 1) & (RC - 1);
+        for (int a = 0; a < kFourierW; ++a) {
+            const float2 bv = col[a];
+            ra.x = fmaf(wy[a], bv.x, ra.x);
+            ra.y = fmaf(wy[a], bv.y, ra.y);
         }
-        if (vw >> 16) acc.y = -acc.y;
-        Y[__float_as_int(e2.w)] = cmul(acc, make_float2(e0.z, e0.w));
+        acc.x = fmaf(wx[c], ra.x, acc.x);
+        acc.y = fmaf(wx[c], ra.y, acc.y);
+        s = (s + 1) & (RC - 1);
     }
+    if (vw >> 16) acc.y = -acc.y;
+    Y[__float_as_int(e2.w)] = cmul(acc, make_float2(e0.z, e0.w));
 }
 
 // Multiples and quotients by a transform length: shifts for powers of two,
-// else plain arithmetic.
-template <bool POW2>
+// else float products with inv = 1 / n (div_small) where the registers allow it
+// (FLOAT): at six waves per SIMD they add to the spills, 80 images at L = 96 54 ->
+// 59 us.
+template <bool POW2, bool FLOAT>
 struct Len {
     int n, lg;
+    float inv;
     __device__ __forceinline__ int mul(int x) const {
         if constexpr (POW2) return x << lg;
         else return x * n;
     }
     __device__ __forceinline__ int div(int x) const {
         if constexpr (POW2) return x >> lg;
+        else if constexpr (FLOAT) return div_small(x, inv);
         else return x / n;
     }
 };
@@ -202,9 +207,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
     extern __shared__ __align__(16) float2 lds2[];
     const int L = S.L, M = L >> 1, n = S.n, Nf = S.Nf, lgNf = S.lgNf, lgL = S.lgL;
     const int G = fourier_group(L), lgG = 31 - __builtin_clz(G), RC = 2 * G, CS = fourier_stride(Nf);
-    const int rounds = fourier_rounds(L), nsl = fourier_slices(S);
+    // with an own slot all phases come at once, in a single round
+    if constexpr (OWN) phases = kRows | kColumns | kSlices, row_parts = 1;
+    const int rounds = OWN ? 1 : fourier_rounds(L), nsl = fourier_slices(S), npts = nsl * (M + 1);
     const float h = 2.f / (float)L;
-    const int tid = threadIdx.x, part = blockIdx.y, parts = gridDim.y;
+    const int tid = threadIdx.x, part = OWN ? 0 : blockIdx.y, parts = OWN ? 1 : gridDim.y;
     float2 *ring = lds2, *temp = ring + fourier_ring(L) * CS;  // [slots][CS], [G or L][CS]
     float2 *twf = temp + min(G, L) * CS;                       // [Nf]
     float2 *cols = ring + fourier_first(L) * CS;               // column 0, the first round's output
@@ -213,12 +220,25 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
     if constexpr (!POW2)
         for (int t = tid; t < L; t += NT) twl[t] = T.twl[t];
     float2 *R;  // [rounds][L][G]
-    if constexpr (OWN) R = POW2 ? twl : twl + L;
-    else R = scratch + (size_t)blockIdx.x * fourier_slot_elems(S);
+    const float2 *shift = T.shift;  // [L], in LDS before an own slot
+    if constexpr (OWN) {
+        float2 *sh = POW2 ? twl : twl + L;
+        for (int t = tid; t < L; t += NT) sh[t] = T.shift[t];
+        shift = sh;
+        R = sh + L;
+    } else {
+        R = scratch + (size_t)blockIdx.x * fourier_slot_elems(S);
+    }
     float2 *CL = R + (size_t)rounds * L * G;  // [2][Nf] column L
     int *flags = (int *)(CL + 2 * Nf);
     float2 *Y = CL + 2 * Nf + kFourierFlags;  // [nsl][M + 1]
-    const Len<POW2> LM{M, lgL - 1}, LL{L, lgL};
+    const Len<POW2, OWN> LM{M, lgL - 1, __builtin_amdgcn_rcpf((float)M)};
+    const Len<POW2, OWN> LL{L, lgL, __builtin_amdgcn_rcpf((float)L)};
+    // this block's share of `count` rounds or pairs
+    auto share = [&](int count, int &from, int &to) {
+        from = count * part / parts;
+        to = count * (part + 1) / parts;
+    };
     // the transforms of length Nf of cnt rows after their first step; that
     // step's output goes to fft_in(target), the result is in target
     const int later = POW2 ? (lgNf - 1) >> 1 : fft_passes(Nf / 4);
@@ -239,8 +259,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
             if (clear && tid == 0 && part == 0) clear[g] = 0u;
             // row pair rp0 + f, columns j and j + M
             const int f = LM.div(tid), j = tid - LM.mul(f);
-            const int rr = (M + G - 1) >> lgG;
-            const int k0 = rr * part / parts, k1 = rr * (part + 1) / parts;
+            const int rr = OWN ? 1 : (M + G - 1) >> lgG;
+            int k0, k1;
+            share(rr, k0, k1);
             const float cl = f < G ? T.corr[j] : 0.f, cr = f < G ? T.corr[j + M] : 0.f;
             int bad = 0;
             float x[4];
@@ -292,7 +313,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
             __syncthreads();
         }
         if (phases & kColumns) {
-            const int k0 = rounds * part / parts, k1 = rounds * (part + 1) / parts;
+            int k0, k1;
+            share(rounds, k0, k1);
             const bool tail = k1 == rounds;  // this block also takes the points at column L
             // column f of the round, rows j and j + M
             const int f = tid & (G - 1), j = tid >> lgG;
@@ -309,13 +331,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
             auto slot = [&](int v) {
                 return ring + __mul24((v + fourier_first(L)) & (RC - 1), CS);
             };
-            const int ka = max(k0 - 1, 0), end = k1 + (tail && fourier_tail(L) ? 1 : 0);
+            const bool after = !OWN && fourier_tail(L);
+            const int ka = max(k0 - 1, 0), end = k1 + (tail && after ? 1 : 0);
             // round 0 first where the copy of column L is needed and it is not
             // one of this block's (which then keeps a copy of its own)
             bool pre = tail && ka > 0;
             float2 *kept = pre ? CL + Nf : CL;
             int k = pre ? 0 : ka;
             fetch(k);
+            Point first{};
+            if constexpr (OWN)
+                if (tid < npts) first = load_point(T.targets, npts, tid);
             while (k < end) {
                 const int next = pre ? ka : k + 1;
                 if (k < rounds) {  // columns k G .. of the spectrum into the ring
@@ -364,7 +390,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
                             }
                     }
                 }
-                if (k == (fourier_tail(L) ? rounds : rounds - 1)) {
+                if (k == (after ? rounds : rounds - 1)) {
                     // column L, and L + 1 .. L + 3: B[u][L + v] = conj B[-u][L - v]
                     if (k > 0)
                         for (int u = tid; u < Nf + 8; u += NT) slot(L)[u] = kept[u < Nf ? u : u - Nf];
@@ -375,9 +401,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
                         }
                 }
                 __syncthreads();
-                if (k >= k0 && !pre)
-                    slice_points<NT>(ring, CS, RC, T.targets, nsl * (M + 1), T.steps[k],
-                                     T.steps[k + 1], Y);
+                if constexpr (OWN) {  // one round: every point
+                    if (tid < npts) slice_point(ring, CS, RC, first, Y);
+                    for (int i = tid + NT; i < npts; i += NT)
+                        slice_point(ring, CS, RC, load_point(T.targets, npts, i), Y);
+                } else if (k >= k0 && !pre) {
+                    const int i1 = T.steps[k + 1];
+                    for (int i = T.steps[k] + tid; i < i1; i += NT)
+                        slice_point(ring, CS, RC, load_point(T.targets, npts, i), Y);
+                }
                 __syncthreads();
                 pre = false;
                 k = next;
@@ -390,7 +422,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
             // slices m < nsl, two per inverse transform: nsl = n/2 with their
             // theta + pi mirrors, or all n (slices at explicit angles)
             const int pairs = nsl >> 1;  // n is a multiple of 8
-            const int p0 = pairs * part / parts, p1 = pairs * (part + 1) / parts;
+            int p0, p1;
+            share(pairs, p0, p1);
             // two work buffers of `most` transforms of length L = Nf / 2
             const int most = 2 * min(G, L);
             float2 *fa = ring, *fb = ring + most * L;
@@ -405,7 +438,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
                         c1.y = -c1.y;
                         c2.y = -c2.y;
                     }
-                    const float2 sh = T.shift[t];
+                    const float2 sh = shift[t];
                     float2 z1 = cmul(c1, sh), z2 = cmul(c2, sh);
                     if (k == 0 || k == -M) {  // self-paired frequencies: real part
                         z1.y = 0.f;
@@ -462,15 +495,31 @@ static bool fourier_own(const FourierShape &S) {
 }
 
 static size_t fourier_lds_bytes(const FourierShape &S) {
-    return fourier_work_bytes(S.L) + (fourier_own(S) ? fourier_slot_bytes(S) : 0);
+    return fourier_work_bytes(S.L) +
+           (fourier_own(S) ? sizeof(float2) * S.L + fourier_slot_bytes(S) : 0);
 }
 
 using FourierKernel = decltype(&k_fourier<512, true, false>);
 
+// Threads of a block.  With an own slot as few as take the rows' first butterflies
+// (M^2) at once and the points in two turns: the rest only wait at the barriers,
+// and with fewer waves a block more images are in flight.  5,000 images at L = 8
+// 53 us with the spectrum in scratch and 512 threads, 63 with it in LDS, 20 with
+// 128 threads; at L = 16 68, 70 and 25.
+static int fourier_nt(const FourierShape &S) {
+    if (!fourier_own(S)) return fourier_threads(S.L);
+    const int M = S.L / 2, npts = fourier_slices(S) * (M + 1);
+    int nt = 128;
+    while (nt < 512 && (nt < M * M || 2 * nt < npts)) nt *= 2;
+    return nt;
+}
+
 static FourierKernel fourier_kernel(const FourierShape &S) {
-    static const FourierKernel ks[6] = {k_fourier<512, false, false>, k_fourier<512, true, false>,
-                                        k_fourier<512, false, true>,  k_fourier<512, true, true>,
-                                        k_fourier<1024, false, false>, k_fourier<1024, true, false>};
+    static const FourierKernel ks[10] = {
+        k_fourier<512, false, false>, k_fourier<512, true, false>, k_fourier<1024, false, false>,
+        k_fourier<1024, true, false>, k_fourier<128, false, true>, k_fourier<128, true, true>,
+        k_fourier<256, false, true>,  k_fourier<256, true, true>,  k_fourier<512, false, true>,
+        k_fourier<512, true, true>};
     static const hipError_t attr = [] {
         for (FourierKernel k : ks)
             (void)hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -479,13 +528,14 @@ static FourierKernel fourier_kernel(const FourierShape &S) {
     }();
     (void)attr;
     const int p2 = lg_exact(S.L) >= 0 ? 1 : 0;
-    return ks[p2 + (fourier_threads(S.L) == 1024 ? 4 : fourier_own(S) ? 2 : 0)];
+    const int nt = fourier_nt(S);
+    return ks[p2 + (fourier_own(S) ? nt == 128 ? 4 : nt == 256 ? 6 : 8 : nt == 1024 ? 2 : 0)];
 }
 
 int fourier_blocks_per_cu(const FourierShape &S) {
     int nb = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nb, (const void *)fourier_kernel(S), fourier_threads(S.L), fourier_lds_bytes(S));
+        &nb, (const void *)fourier_kernel(S), fourier_nt(S), fourier_lds_bytes(S));
     return e == hipSuccess && nb > 0 ? nb : 1;
 }
 
@@ -493,7 +543,7 @@ hipError_t launch_fourier(const float *img, int64_t N, const FourierShape &S, co
                           void *scratch, int slots, bool few, float *pmf, hipStream_t s,
                           unsigned *clear) {
     if (N <= 0) return hipSuccess;
-    const int L = S.L, NT = fourier_threads(L);
+    const int L = S.L, NT = fourier_nt(S);
     const size_t lds = fourier_lds_bytes(S);
     const FourierKernel k = fourier_kernel(S);
     float2 *scr = (float2 *)scratch;
