@@ -143,41 +143,45 @@ __global__ __launch_bounds__(NT) void k_project_few(const float *__restrict__ im
         for (int t = threadIdx.x; t < n * L; t += NT) out[t] = __int_as_float(0x7fc00000);
 }
 
-// Two images per block for geometries of more tasks than the kernels above
-// hold at once (more than 72; L = n = 256 has 132): 1024 threads and strips of
-// 70 KiB per image, one block per compute unit, five tasks per wave, in as
-// many groups as it takes (each stages the images again).  The accumulation is
-// bound by the VALU: sharing the weights between two images takes it from
-// 21.5 to 16.75 instructions per row and image, and the four-kind strips from
-// four LDS reads per row to three.  1,500 images at L = n = 256 2.31 -> 1.61
-// ms against the one-image kernel on sliding windows (nine tasks per wave);
-// all tasks in one group, with nine per wave, or eleven of 768 threads, spill:
-// 1.64-1.87 ms.  Bitwise the projections of k_project.
-constexpr int kImg2BytesLarge = 70 * 1024;
+// Geometries of more tasks than the kernels above hold at once (more than 72;
+// L = n = 256 has 132): 1024 threads and 140 KiB of strips, one block per compute
+// unit, in as many groups of tasks as it takes (each stages the images again).
+// The accumulation is bound by the VALU: sharing the weights between two images
+// takes it from 21.5 to 16.75 instructions per row and image, and the four-kind
+// strips from four LDS reads per row to three.  1,500 images at L = n = 256 2.31
+// -> 1.61 ms with two images of five tasks per wave against the one-image kernel
+// on sliding windows (nine tasks per wave); all tasks in one group, with nine per
+// wave, or eleven of 768 threads, spill: 1.64-1.87 ms.  One image per block, of
+// nine tasks per wave, where every image has a compute unit of its own: 256
+// images 498 us on sliding windows, 509 with two images on every second unit, 296
+// so.  Bitwise the projections of k_project.
+constexpr int kLargeStrips = 140 * 1024;
 
-template <int NT, int TPW>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_project2_large(
+template <int NT, int TPW, int IMG>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_project_large(
     const float *__restrict__ img, int64_t N, ProjShape P, const float2 *__restrict__ dtab,
     float *__restrict__ pmf) {
-    constexpr int IB = kImg2BytesLarge;
+    constexpr int IB = kLargeStrips / IMG, KP = 4 / IMG;
     constexpr int NW = NT / 64;
     extern __shared__ __align__(16) float lds[];
-    const int64_t g0 = 2 * (int64_t)blockIdx.x;
+    const int64_t g0 = IMG * (int64_t)blockIdx.x;
     if (g0 >= N) return;
-    const int nimg = N - g0 >= 2 ? 2 : 1;
+    const int nimg = N - g0 >= IMG ? IMG : 1;
     const int L = P.L, n = P.n;
-    const float *F[2] = {img + g0 * (int64_t)L * L, img + (g0 + nimg - 1) * (int64_t)L * L};
-    // the slot table after both images' strips (an opaque offset, as above)
-    int off = 2 * (IB / 4);
+    const float *F[IMG];
+#pragma unroll
+    for (int g = 0; g < IMG; ++g) F[g] = img + (g0 + min(g, nimg - 1)) * (int64_t)L * L;
+    // the slot table after the strips (an opaque offset, as above)
+    int off = kLargeStrips / 4;
     asm volatile("" : "+s"(off));
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int tg0 = 0; tg0 < P.ntasks; tg0 += NW * TPW) {
-        float acc[2][TPW][4];
-        int bad[2];
-        project_images2<NT, TPW, 2, 2, IB>(F, nimg, P, dtab, lds, (float4 *)(lds + off),
-                                           s4_rows<NT>(L, IB), tg0, acc, bad);
+        float acc[IMG][TPW][4];
+        int bad[IMG];
+        project_images2<NT, TPW, IMG, KP, IB>(F, nimg, P, dtab, lds, (float4 *)(lds + off),
+                                              s4_rows<NT, KP>(L, IB), tg0, acc, bad);
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
+        for (int g = 0; g < IMG; ++g) {
             if (g < nimg) {  // block-uniform
                 float *out = pmf + (g0 + g) * (int64_t)n * L;
                 if (!bad[g])
@@ -236,18 +240,22 @@ static hipError_t launch_project_few_t(const float *img, int64_t N, const ProjSh
     return hipGetLastError();
 }
 
-static hipError_t launch_project_few(const float *img, int64_t N, const ProjShape &P,
-                                     const float2 *dtab, float *pmf, unsigned *clear,
-                                     hipStream_t s) {
-    constexpr int NT = 512;
+static int device_cus() {
     static const int cus = [] {
         int dev = 0, c = 0;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev);
         return c > 0 ? c : 256;
     }();
+    return cus;
+}
+
+static hipError_t launch_project_few(const float *img, int64_t N, const ProjShape &P,
+                                     const float2 *dtab, float *pmf, unsigned *clear,
+                                     hipStream_t s) {
+    constexpr int NT = 512;
     const int groups = (P.ntasks + NT / 64 - 1) / (NT / 64);
-    const int bytes = N * groups <= cus ? 140 * 1024 : 64 * 1024;
+    const int bytes = N * groups <= device_cus() ? 140 * 1024 : 64 * 1024;
     const int most = s4_rows<NT, 8>(P.L, bytes), strips = (P.L + most - 1) / most;
     const int R = (P.L + strips - 1) / strips;  // <= most: strips of nearly equal height
     if (s4_rows<NT, 2>(P.L, bytes) >= R)
@@ -257,16 +265,16 @@ static hipError_t launch_project_few(const float *img, int64_t N, const ProjShap
     return launch_project_few_t<NT, 8>(img, N, P, R, dtab, pmf, clear, s);
 }
 
-template <int NT, int TPW>
-static hipError_t launch_project2_large(const float *img, int64_t N, const ProjShape &P,
-                                        const float2 *dtab, float *pmf, hipStream_t s) {
-    const size_t lds = 2 * (size_t)kImg2BytesLarge + sizeof(float4) * (P.slots + 1);
+template <int NT, int TPW, int IMG>
+static hipError_t launch_project_large(const float *img, int64_t N, const ProjShape &P,
+                                       const float2 *dtab, float *pmf, hipStream_t s) {
+    const size_t lds = (size_t)kLargeStrips + sizeof(float4) * (P.slots + 1);
     static const hipError_t attr = hipFuncSetAttribute(
-        (const void *)k_project2_large<NT, TPW>,
-        hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+        (const void *)k_project_large<NT, TPW, IMG>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        152 * 1024);
     (void)attr;
-    hipLaunchKernelGGL((k_project2_large<NT, TPW>), dim3((unsigned)((N + 1) / 2)), dim3(NT), lds, s,
-                       img, N, P, dtab, pmf);
+    hipLaunchKernelGGL((k_project_large<NT, TPW, IMG>), dim3((unsigned)((N + IMG - 1) / IMG)),
+                       dim3(NT), lds, s, img, N, P, dtab, pmf);
     return hipGetLastError();
 }
 
@@ -294,7 +302,8 @@ hipError_t launch_project(const float *img, int64_t N, Geo g, const AngleTable &
     if (w512 <= 5) return launch_project_t<512, 5>(img, N, P, t.d32, pmf, s);
     if (w512 <= 6) return launch_project_t<512, 6>(img, N, P, t.d32, pmf, s);
     if (w512 <= 9) return launch_project_t<512, 9>(img, N, P, t.d32, pmf, s);
-    return launch_project2_large<1024, 5>(img, N, P, t.d32, pmf, s);
+    if (N <= device_cus()) return launch_project_large<1024, 9, 1>(img, N, P, t.d32, pmf, s);
+    return launch_project_large<1024, 5, 2>(img, N, P, t.d32, pmf, s);
 }
 
 }  // namespace sw

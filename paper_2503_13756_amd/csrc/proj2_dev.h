@@ -72,7 +72,7 @@ struct Strip4Regs {
 };
 
 // Quotient and remainder of e by w through a multiply-high with
-// mg = floor((2^32 - 1) / w) + 1: exact while e w < 2^32 (e < 512, w <= 1024
+// mg = floor((2^32 - 1) / w) + 1: exact while e w < 2^32 (e < 1024, w <= 1024
 // here).  mg is uniform, so each division is one VALU operation with a scalar
 // operand.  For w = 1 the multiplier (2^32) does not fit: mg = 0 there and the
 // quotient is e itself.
