@@ -64,7 +64,7 @@ __device__ void reference_spectrum(const MixItem &it, const float *T, float2 *ld
 template <int NT, int TPW>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tables_mixed(
     const MixGroup *__restrict__ G0, const MixGroup *__restrict__ G1, unsigned long long *counter,
-    float *scratch, int64_t slot_floats, int region_floats, int /*lmax*/, int nmax) {
+    float *scratch, int64_t slot_floats, int region_floats, int nmax) {
     constexpr int NW = NT / 64;
     extern __shared__ __align__(16) double ldsd[];  // 16-byte aligned: ds_read_b128 on strips
     __shared__ int64_t wslot;
@@ -215,7 +215,7 @@ MixLaunch plan_mixed(MixItem *items, int nitems, MixKnobs knobs) {
     constexpr int NTT = kMixTablesThreads, TPW = kMixTablesTasks;  // tables kernel
     MixLaunch m{};
     m.tpw = kMixTablesTasksSmall;
-    int lmax = 8, nmax = 8, region = 0;
+    int nmax = 8, region = 0;
     int64_t slot = 0;
     size_t align_lds = 0;
     for (int i = 0; i < nitems; ++i) {
@@ -235,7 +235,6 @@ MixLaunch plan_mixed(MixItem *items, int nitems, MixKnobs knobs) {
         it.fused = one_group && pmf <= kStripFloats ? 1 : 0;
         region = max(region, it.fused ? max(strip, pmf) : strip);
         if (!it.fused) slot = max(slot, (int64_t)pmf);
-        lmax = max(lmax, it.L);
         nmax = max(nmax, it.n);
         align_lds = max(align_lds, align_pairs_lds(it.n, 1));
     }
@@ -265,7 +264,6 @@ MixLaunch plan_mixed(MixItem *items, int nitems, MixKnobs knobs) {
     }
     m.align_bpc = knobs.align_bpc >= 1 && knobs.align_bpc <= 8 ? knobs.align_bpc : 8;
     m.region_floats = region;
-    m.lmax = lmax;
     m.nmax = nmax;
     m.tables_lds = fixed + sizeof(float) * qmax;
     m.slot_floats = slot;
@@ -306,15 +304,15 @@ hipError_t launch_mixed(const MixGroup *d_refs, const MixGroup *d_imgs, const Mi
     if (m.tpw == kMixTablesTasksSmall)
         hipLaunchKernelGGL((k_tables_mixed<NTT, kMixTablesTasksSmall>), dim3((unsigned)grid),
                            dim3(NTT), m.tables_lds, s, d_refs, d_imgs, counters + 0, scratch,
-                           m.slot_floats, m.region_floats, m.lmax, m.nmax);
+                           m.slot_floats, m.region_floats, m.nmax);
     else if (m.tpw == kMixTablesTasksLarge)
         hipLaunchKernelGGL((k_tables_mixed<NTT, kMixTablesTasksLarge>), dim3((unsigned)grid),
                            dim3(NTT), m.tables_lds, s, d_refs, d_imgs, counters + 0, scratch,
-                           m.slot_floats, m.region_floats, m.lmax, m.nmax);
+                           m.slot_floats, m.region_floats, m.nmax);
     else
         hipLaunchKernelGGL((k_tables_mixed<NTT, TPW>), dim3((unsigned)grid), dim3(NTT),
                            m.tables_lds, s, d_refs, d_imgs, counters + 0, scratch,
-                           m.slot_floats, m.region_floats, m.lmax, m.nmax);
+                           m.slot_floats, m.region_floats, m.nmax);
     hipLaunchKernelGGL((k_refspec_mixed<NT>), dim3((unsigned)kMaxMix), dim3(NT),
                        sizeof(float2) * (kMaxN + 2 * kFftElems), s, d_imgs);
     // four 37 KiB blocks of four waves of the register-FFT kernel per compute unit

@@ -57,7 +57,10 @@ __global__ __launch_bounds__(NT) void k_quantile_rf(const float *__restrict__ pf
 // done[g] counts the finished blocks of image g; 0 before the launch (the
 // projectors clear it).  The sums are stored and read as device-scope atomics,
 // past the caches that the dies do not share, and a block counts once its
-// stores are acknowledged.  (With plain stores and a device-scope fence a block,
+// stores are acknowledged.  That a store so acknowledged is seen by every die's
+// later device-scope load is a property of this hardware (write-through at
+// device scope, and a wait that covers stores), not of the memory model, which
+// would ask for release and acquire.  (With plain stores and a device-scope fence a block,
 // the fences' cache write-backs took 35 ns a block one after the other: 200
 // images at L = n = 64 55 us, now 8.)
 constexpr int kColsPerBlock = 8;

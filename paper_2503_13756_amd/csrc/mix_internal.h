@@ -48,7 +48,7 @@ struct MixGroup {
     MixItem items[kMaxMix];
 };
 struct MixLaunch {
-    int region_floats, lmax, nmax;
+    int region_floats, nmax;
     int tpw;  // tasks per wave of the tables kernel instance
     size_t tables_lds;
     int64_t slot_floats;

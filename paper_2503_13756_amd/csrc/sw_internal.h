@@ -153,7 +153,7 @@ struct PairArgs {
     float *curve;  // nullable
 };
 hipError_t launch_align_pairs(const PairArgs &a, Geo g, const AngleTable &t, hipStream_t s);
-// Max-sliced alignment (rotation only) of every pair: n = 64 or 128.
+// Max-sliced alignment (rotation only) of every pair: n a multiple of 16 up to 128.
 bool msw_supported(Geo g);
 hipError_t launch_align_msw(const PairArgs &a, Geo g, hipStream_t s);
 // The same for n = 128 with register-resident angle FFTs, from the references'
