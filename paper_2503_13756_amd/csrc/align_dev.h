@@ -143,8 +143,8 @@ __device__ __forceinline__ void store_gamma128(float2 *gam, float2 *gx, int p, i
 // integer divisions here), the transforms and the rescore.  Sharing the image's
 // transforms between references takes the transforms, two thirds of a pair's
 // work at n = 64, out of all but one of them.  16 x 2,000 pairs at L = n = Q = 64
-// 517 -> 142 us; one reference against 1,500 images at 256 508 -> 322 us, against
-// 1,031 at L = 39 22 -> 18 us.
+// 517 -> 128 us; one reference against 1,500 images at 256 508 -> 300 us, against
+// 1,031 at L = 39 22 -> 15 us.
 struct PairsJob {
     const float *U, *V;    // [nr][Q][n] and [Q][n] tables
     const double *au, *av; // aux of both, [nr][4] and [4]

@@ -24,8 +24,8 @@
 // residual is 4,096 subtractions and multiply-adds at n = 64, and four of them
 // a pair were nine tenths of the call; k_corr_mfma therefore drops the
 // candidates that its estimate and the rounding errors of the bf16 spectra
-// prove not to be the minimum (1.24 of 4 are left on noisy copies of one
-// object): 2,000 x 2,000 at L = 64 5.44 -> 2.54 ms.
+// prove not to be the minimum (1.1 to 1.5 of 4 are left on noisy copies of one
+// object): 2,000 x 2,000 at L = 64 5.45 -> 2.45 ms.
 #include "sw_internal.h"
 #include "wave_dev.h"
 
