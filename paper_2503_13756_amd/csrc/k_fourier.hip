@@ -348,7 +348,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 &&
                     float2 *dst = cols + (k & 1) * G * CS;
                     const int cnt = min(G, L - k * G);
                     if (j < M && f < cnt) first_step(fft_in(dst) + __mul24(f, CS), j, hi, lo);
-                    // (32 < L <= 36: more than one butterfly per thread)
+                    // (fewer threads than the round's butterflies: L = 36, own slots)
                     for (int jj = j + (NT >> lgG); jj < M; jj += NT >> lgG)
                         if (f < cnt) {
                             const float2 *p = R + (size_t)k * L * G + (jj << lgG) + f;
